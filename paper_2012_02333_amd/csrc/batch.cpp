@@ -41,7 +41,7 @@ struct BatchBuild {
   std::vector<MassDesc> mass;
   struct G {
     int level, mode, cfg;
-    bool small, strip;
+    bool small, strip, panel;
     int xent;
     Acc acc;
     std::vector<std::pair<double, ContractArgs>> steps;  // (cost, args)
@@ -64,11 +64,12 @@ struct BatchBuild {
 // 2^20, 3.94 with 2^19, 3.96 with 2^17 and 2^18.  Such a step's outputs then
 // differ from the single call's by FP32 rounding (another product order).
 static constexpr int kBatchWideLog = 19;
-static int queue_cfg(Acc acc, const Step &st, int mode, bool out_double) {
+static int queue_cfg(Acc acc, const Plan &p, size_t si, int mode, bool out_double) {
+  const Step &st = p.steps[si];
   const Acc sa = step_acc(acc, st.wide_ok(), (int)st.S.size());
   const int nS = (int)st.S.size();
-  int c = choose_tile(sa, nS, st.logM, st.logN, st.wide_ok(), st.nbatch);
-  if (sa == Acc::F32 && st.wide_ok() && nS >= 3 && st.logM >= 7 && st.logN >= 7 &&
+  int c = choose_tile(sa, nS, st.logM, st.logN, st.wide_ok(), panel_step(p, si), st.nbatch);
+  if (sa == Acc::F32 && st.wide_ok() && nS >= 3 && (panel_step(p, si) || (st.logM >= 7 && st.logN >= 7)) &&
       (int64_t(1) << (st.logM + st.logN)) * st.nbatch >= (int64_t(1) << kBatchWideLog))
     c = kTileW;
   int tc = 0, xcd = 0;
@@ -151,7 +152,7 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
       a.nRX = (int)st.RX.size();
       a.nRY = (int)st.RY.size();
       const int step_mode = !last ? kModeIntermediate : (is_blocked(p, st) ? kModeFinalBlocked : kModeFinalDeposit);
-      const int cfg = queue_cfg(B.acc, st, step_mode, acc_double);
+      const int cfg = queue_cfg(B.acc, p, s, step_mode, acc_double);
       const TileShape sh = tile_shape(cfg);
       a.tilesM = (int)(((int64_t(1) << st.logM) + sh.bm - 1) / sh.bm);
       a.tilesN = (int)(((int64_t(1) << st.logN) + sh.bn - 1) / sh.bn);
@@ -159,6 +160,8 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
       a.mx = to_dev(st.mx);
       a.my = to_dev(st.my);
       set_lists(L, s, ws, &a);
+      const Acc sa = step_acc(B.acc, st.wide_ok(), (int)st.S.size());
+      a.panel = cfg == kTileW && sa == Acc::F32 && panel_step(p, s) ? 1 : 0;
       int level = (int)s;
       if (!last) {
         a.mode = kModeIntermediate;
@@ -192,13 +195,12 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
           a.partials = reinterpret_cast<double *>(ws + L.partials_off);
           MassDesc md;
           md.partials = a.partials;
-          md.count = kPartialsPerTile * a.nblocks;
+          md.count = mass_partials(cfg, a, true);
           md.mass = sum_to;
           B.mass.push_back(md);
         }
       }
       const bool small = a.nS <= 2;
-      const Acc sa = step_acc(B.acc, st.wide_ok(), (int)st.S.size());
       // FP32 small-term steps over whole 64 x 256 tiles in pairs of rows run as
       // two-tile strips with every term kept (dead terms add exact zeros) -
       // for instances whose one-instance call computes no row flags, so the
@@ -208,7 +210,7 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
       if (strip) a.flagX = a.flagY = nullptr;
       // cross-entropy form of the final step: 1 gradient, 2 gradient and loss
       const int xe = xent == nullptr || !last ? 0 : (xent->losses && xent->losses[i] ? 2 : 1);
-      auto key = std::make_tuple(level, (int)a.mode, cfg, (int)small * 2 + (int)strip, (int)sa, xe);
+      auto key = std::make_tuple(level, (int)a.mode, cfg, (int)small * 2 + (int)(strip || a.panel), (int)sa, xe);
       auto it = gidx.find(key);
       if (it == gidx.end()) {
         it = gidx.emplace(key, B.groups.size()).first;
@@ -218,6 +220,7 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
         g.cfg = cfg;
         g.small = small;
         g.strip = strip;
+        g.panel = a.panel != 0;
         g.xent = xe;
         g.acc = sa;
         B.groups.push_back(g);
@@ -290,6 +293,7 @@ static Status batch_run(cqc_batch_s *b, hipStream_t s) {
     q.bprefix = G.bprefix;
     q.btotal = G.btotal;
     q.xent = G.xent;
+    q.panel = G.panel;
     if (G.strip) CQC_TRY(launch_contract_strip_queue(G.mode, q, s));
     else CQC_TRY(launch_contract_queue(G.acc, G.mode, G.cfg, G.small, q, s));
   }
@@ -333,7 +337,8 @@ static Status batch_create(const cqc_instance *inst, int32_t n_inst, cqc_dtype i
     for (auto &st : G.steps) {
       descs.push_back(st.second);
       const int64_t nb = st.second.nblocks;
-      prefix.push_back(prefix.back() + (G.strip   ? nb / kStripRows
+      prefix.push_back(prefix.back() + (G.panel ? (panel_partials(st.second, true) + 3) / 4
+                                        : G.strip ? nb / kStripRows
                                         : G.small ? (nb + kSmallTilesPerItem - 1) / kSmallTilesPerItem
                                                   : nb));
       bprefix.push_back(bprefix.back() + st.second.nbatch);
@@ -347,6 +352,7 @@ static Status batch_create(const cqc_instance *inst, int32_t n_inst, cqc_dtype i
     bg.cfg = G.cfg;
     bg.small = G.small;
     bg.strip = G.strip;
+    bg.panel = G.panel;
     bg.xent = G.xent;
     bg.acc = G.acc;
     bg.descs = reinterpret_cast<const ContractArgs *>(ws + B.desc_off[g]);

@@ -35,9 +35,10 @@ NetLayout layout_net(const Plan &plan, Acc acc, size_t base) {
     }
   }
   int64_t max_final_blocks = 1;
-  for (const auto &st : plan.steps) {
+  for (size_t i = 0; i < plan.steps.size(); ++i) {
+    const Step &st = plan.steps[i];
     int cfg = choose_tile(step_acc(acc, st.wide_ok(), (int)st.S.size()), (int)st.S.size(), st.logM, st.logN,
-                          st.wide_ok(), st.nbatch);
+                          st.wide_ok(), panel_step(plan, i), st.nbatch);
     TileShape sh = tile_shape(cfg);
     int64_t tm = ((int64_t(1) << st.logM) + sh.bm - 1) / sh.bm;
     int64_t tn = ((int64_t(1) << st.logN) + sh.bn - 1) / sh.bn;
@@ -188,14 +189,19 @@ Status run_net(const NetLayout &L, char *ws, const std::vector<const void *> &en
     const int mode = !last ? kModeIntermediate : (is_blocked(p, st) ? kModeFinalBlocked : kModeFinalDeposit);
     const bool od = last ? out_double : L.acc == Acc::F64;
     const Acc sa = step_acc(L.acc, st.wide_ok(), (int)st.S.size());
-    int cfg = L.tile[i], xcd = 0;
+    a.panel = sa == Acc::F32 && panel_step(p, i) && !od ? 1 : 0;
+    // (the layout does not know the output dtype, which the panel kernel needs to be FP32)
+    const int rule = od && sa == Acc::F32 && L.tile[i] == kTileW
+                         ? choose_tile(sa, a.nS, st.logM, st.logN, st.wide_ok(), false, st.nbatch) : L.tile[i];
+    int cfg = rule, xcd = 0;
     // a cached choice is keyed by shape class, which does not fix the operand
     // heights: the wide tile also needs this step's operands to fit it
     if (!tuned_choice(sa, mode, a.nS <= 2, st.logM, st.logN, a.nS, od, &cfg, &xcd) || !tile_ok(sa, cfg) ||
         (cfg == kTileW && !st.wide_ok())) {
-      cfg = L.tile[i];
+      cfg = rule;
       // the wide kernel's tiles of one operand row block share that block's
-      // operand columns: keep them on one XCD (and its L2)
+      // operand columns: keep them on one XCD (and its L2); so do the panel
+      // kernel's units of one row run
       xcd = cfg == kTileW ? 1 : 0;
     }
     const TileShape sh = tile_shape(cfg);
@@ -238,7 +244,7 @@ Status run_net(const NetLayout &L, char *ws, const std::vector<const void *> &en
       }
       if (mass) a.partials = reinterpret_cast<double *>(ws + L.partials_off);
       CQC_TRY(launch_contract(sa, out_double, cfg, a, s));
-      if (mass) CQC_TRY(launch_mass_final(a.partials, kPartialsPerTile * a.nblocks, mass, s, gate, gate_val));
+      if (mass) CQC_TRY(launch_mass_final(a.partials, mass_partials(cfg, a, false), mass, s, gate, gate_val));
     }
   }
   return Status::ok();

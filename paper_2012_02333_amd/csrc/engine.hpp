@@ -58,4 +58,9 @@ inline bool is_blocked(const Plan &p, const Step &st) {
   return true;
 }
 
+// Whether step i of a plan fits the panel kernel (which does not write in deposit order).
+inline bool panel_step(const Plan &p, size_t i) {
+  return p.steps[i].panel_ok() && (i + 1 < p.steps.size() || is_blocked(p, p.steps[i]));
+}
+
 }  // namespace cqc

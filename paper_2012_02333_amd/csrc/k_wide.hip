@@ -121,28 +121,6 @@ __global__ __launch_bounds__(256) void k_label_list_table(const ContractArgs *de
   label_list(descs[d], (int64_t)blockIdx.x - bprefix[d]);
 }
 
-// Values the compiler cannot prove wave-uniform (loaded through pointers the
-// kernel could in principle write) moved to scalar registers.
-__device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int64_t uni(int64_t v) {
-  return (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)v) |
-         ((int64_t)__builtin_amdgcn_readfirstlane((int32_t)(v >> 32)) << 32);
-}
-template <typename T> __device__ __forceinline__ T *uni(T *p) {
-  return reinterpret_cast<T *>(uni((int64_t)reinterpret_cast<uintptr_t>(p)));
-}
-__device__ __forceinline__ double uni(double v) { return __builtin_bit_cast(double, uni(__builtin_bit_cast(int64_t, v))); }
-// Global-address-space view of a pointer (a pointer that went through an
-// integer is generic to the compiler, which would emit flat accesses).
-template <typename T> using gptr = __attribute__((address_space(1))) T *;
-template <typename T> __device__ __forceinline__ gptr<T> gbl(T *p) { return (gptr<T>)p; }
-// Constant-address-space view of data that no wave writes during the kernel
-// (label lists and counts, written by the preceding label-list pass): uniform
-// loads through it become scalar loads, which are waited for on the scalar
-// counter - not behind this wave's outstanding output stores.
-template <typename T> using cptr = __attribute__((address_space(4))) const T *;
-template <typename T> __device__ __forceinline__ cptr<T> cst(const T *p) { return (cptr<T>)gbl(p); }
-
 // ---- a tile of a step: its block index and chunk count; the geometry is
 // recomputed from the step's arguments where it is needed (few scalars live)
 struct WideTile {
@@ -779,6 +757,17 @@ static Status launch_persistent(const char *nm, K kernel, const ContractArgs &a,
   return launch(nm, kernel, dim3((unsigned)G), dim3(256), 0, s, a);
 }
 
+Status launch_label_list(const ContractArgs &a, hipStream_t s) {
+  if (!a.lists || !a.counts || a.nbatch < 1 || a.list_ld < wide_list_ld(a.nS))
+    return Status::fail(CQC_ERR_INVALID_ARG, "contraction without label-list workspace");
+  return launch("label_list", k_label_list, dim3((unsigned)a.nbatch), dim3(256), 0, s, a);
+}
+
+Status launch_label_list_table(const QueueLaunch &q, hipStream_t s) {
+  return launch("label_list_table", k_label_list_table, dim3((unsigned)q.btotal), dim3(256), 0, s, q.descs, q.bprefix,
+                q.ndesc);
+}
+
 template <int NP> struct WideNames;
 template <> struct WideNames<0> {
   static constexpr const char *fin = "wide_f32_final", *mid = "wide_f32_inter", *queue = "wide_f32_queue",
@@ -802,7 +791,7 @@ static Status launch_wide_ps(const ContractArgs &a, hipStream_t s) {
 
 template <int NP, typename O>
 static Status launch_wide_t(const ContractArgs &a, hipStream_t s) {
-  CQC_TRY(launch("label_list", k_label_list, dim3((unsigned)a.nbatch), dim3(256), 0, s, a));
+  CQC_TRY(launch_label_list(a, s));
   if constexpr (NP > 0) {
     if (a.Xs && a.Ys) return launch_wide_ps<NP, O, true>(a, s);
   }
@@ -815,8 +804,7 @@ static Status launch_wide_np(bool out_double, const ContractArgs &a, hipStream_t
 }
 
 Status launch_contract_wide(int parts, bool out_double, const ContractArgs &a, hipStream_t s) {
-  if (!a.lists || !a.counts || a.nbatch < 1 || a.list_ld < wide_list_ld(a.nS))
-    return Status::fail(CQC_ERR_INVALID_ARG, "wide contraction without label-list workspace");
+  if (parts == 0 && a.panel && !out_double) return launch_panel(a, s);
   if (!wide_fits(a))
     return Status::fail(CQC_ERR_UNSUPPORTED, "wide contraction: an operand has one column or exceeds 2^30 elements");
   switch (parts) {
@@ -846,8 +834,7 @@ template <int NP>
 static Status launch_wide_queue_t(int mode, const QueueLaunch &q, hipStream_t s) {
   const dim3 grid(q.grid), block(256);
   const char *nm = WideNames<NP>::queue;
-  CQC_TRY(launch("label_list_table", k_label_list_table, dim3((unsigned)q.btotal), block, 0, s, q.descs, q.bprefix,
-                 q.ndesc));
+  CQC_TRY(launch_label_list_table(q, s));
   const char *nx = WideNames<NP>::qx;
   if (mode != kModeIntermediate && q.xent) {
     if (mode == kModeFinalBlocked)
@@ -865,6 +852,7 @@ static Status launch_wide_queue_t(int mode, const QueueLaunch &q, hipStream_t s)
 
 Status launch_contract_wide_queue(int parts, int mode, const QueueLaunch &q, hipStream_t s) {
   if (!q.bprefix || q.btotal < 1) return Status::fail(CQC_ERR_INVALID_ARG, "wide queue without label-list table");
+  if (parts == 0 && q.panel) return launch_panel_queue(mode, q, s);
   switch (parts) {
     case 0: return launch_wide_queue_t<0>(mode, q, s);
     case 2: return launch_wide_queue_t<2>(mode, q, s);

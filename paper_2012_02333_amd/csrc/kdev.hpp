@@ -10,6 +10,28 @@ namespace cqc {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
+// Values the compiler cannot prove wave-uniform (loaded through pointers the
+// kernel could in principle write) moved to scalar registers.
+__device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t uni(int64_t v) {
+  return (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)v) |
+         ((int64_t)__builtin_amdgcn_readfirstlane((int32_t)(v >> 32)) << 32);
+}
+template <typename T> __device__ __forceinline__ T *uni(T *p) {
+  return reinterpret_cast<T *>(uni((int64_t)reinterpret_cast<uintptr_t>(p)));
+}
+__device__ __forceinline__ double uni(double v) { return __builtin_bit_cast(double, uni(__builtin_bit_cast(int64_t, v))); }
+// Global-address-space view of a pointer (a pointer that went through an
+// integer is generic to the compiler, which would emit flat accesses).
+template <typename T> using gptr = __attribute__((address_space(1))) T *;
+template <typename T> __device__ __forceinline__ gptr<T> gbl(T *p) { return (gptr<T>)p; }
+// Constant-address-space view of data that no wave writes during the kernel
+// (label lists and counts, written by the preceding label-list pass): uniform
+// loads through it become scalar loads, which are waited for on the scalar
+// counter - not behind this wave's outstanding output stores.
+template <typename T> using cptr = __attribute__((address_space(4))) const T *;
+template <typename T> __device__ __forceinline__ cptr<T> cst(const T *p) { return (cptr<T>)gbl(p); }
+
 template <typename T> struct MfmaOp;
 // Accumulator layout of one 16x16 block (measured by k_selftest_mfma):
 //   FP32: lane l, register r holds row 4*(l/16) + r   (4 consecutive rows)
@@ -97,7 +119,12 @@ template <> __device__ __forceinline__ void store4<double>(double *p, const doub
 constexpr double kXentFloor = 1e-30;
 template <typename T>
 __device__ __forceinline__ T xent_grad_of(T p, T t) {
-  return (double)p > kXentFloor ? -t / p : T(0);
+  // divided first and selected afterwards: as a conditional division the
+  // compiler makes one branch per output of it, which keeps the epilogues from
+  // being scheduled around their loads and stores
+  T q = -t / p;
+  asm volatile("" : "+v"(q));
+  return (double)p > kXentFloor ? q : T(0);
 }
 
 // Partial-sum contribution of one output p of a cross-entropy final step

@@ -55,6 +55,7 @@ struct ContractArgs {
   int32_t *lists;    // [nbatch][2][list_ld] byte offsets of the live terms' X rows, then of
                      //   their Y rows, ascending s; padding 0
   int32_t *counts;   // [nbatch] live labels
+  int32_t panel;     // 1: a wide step that runs on the panel kernel (every step of a queue group alike)
   int32_t list_ld;   // pairs per batch entry: 4^nS rounded up to a multiple of 32
   int64_t nbatch;
   // device-side predicate: when gate is set, the launch does nothing unless
@@ -125,7 +126,8 @@ inline int split_parts(Acc a) { return a == Acc::BF16X6 ? 3 : a == Acc::BF16X3 ?
 
 // Tile configurations of the contraction kernels: L, M, S, T select the
 // register-operand kernel (FP32 and FP64), W the LDS-staged wide kernel
-// (FP32 and the split forms; the only one the split forms run on).
+// (FP32 and the split forms; the only one the split forms run on) or, for
+// steps that fit it (ContractArgs::panel), the panel kernel.
 enum TileCfg : int32_t { kTileL = 0, kTileM = 1, kTileS = 2, kTileT = 3, kTileW = 4, kTileCount = 5 };
 struct TileShape { int bm, bn; };
 TileShape tile_shape(int cfg);
@@ -133,7 +135,8 @@ TileShape tile_shape(int cfg);
 // wide_ok: both operands fit the wide kernel's addressing (wide_fits).
 // nbatch: batch entries of the step (the wide kernel needs enough 128 x 128
 // tiles over all of them to fill the chip).
-int choose_tile(Acc acc, int nS, int logM, int logN, bool wide_ok, int64_t nbatch);
+// panel: the step runs on the panel kernel where its tile is W.
+int choose_tile(Acc acc, int nS, int logM, int logN, bool wide_ok, bool panel, int64_t nbatch);
 // Whether the arithmetic has a kernel with this tile configuration.
 bool tile_ok(Acc acc, int cfg);
 // Arithmetic a step of a plan runs in.  A split-form step runs the FP32 form
@@ -161,6 +164,7 @@ struct QueueLaunch {
   uint32_t grid;
   const int64_t *bprefix;  // wide kernel: bprefix[d] = first batch entry of step d over the table
   int64_t btotal;          //   and the total (one label-list block per batch entry)
+  bool panel = false;      // wide steps of the panel kernel
   int xent = 0;            // final steps of the cross-entropy form (ContractArgs::xt):
                            //   1 gradient (partials sum p), 2 gradient and loss
 };
@@ -183,6 +187,26 @@ Status launch_row_flags_table(const FlagDesc *descs, int32_t n, int64_t total_bl
 Status launch_mass_table(const MassDesc *descs, int32_t n, hipStream_t s);
 Status launch_contract(Acc acc, bool out_double, int cfg, const ContractArgs &a, hipStream_t s);
 Status launch_contract_wide(int parts, bool out_double, const ContractArgs &a, hipStream_t s);
+// The live-label lists of a step (of every step of a queue launch) of the wide
+// and panel kernels.
+Status launch_label_list(const ContractArgs &a, hipStream_t s);
+Status launch_label_list_table(const QueueLaunch &q, hipStream_t s);
+// Panel kernel (k_panel.hip): the wide steps with ContractArgs::panel set.
+Status launch_panel(const ContractArgs &a, hipStream_t s);
+Status launch_panel_queue(int mode, const QueueLaunch &q, hipStream_t s);
+// Its units: four per block or queue item, one FP64 partial each in a final step.
+int64_t panel_partials(const ContractArgs &a, bool queue);
+// Row tiles per unit (log2) of a queue launch: at most 2^kPanelQueueLog, so that
+// a step of 2^19 outputs still gives 32 waves and large ones reload a panel
+// only every eighth tile.
+constexpr int kPanelQueueLog = 3;
+__host__ __device__ inline int panel_queue_log_tiles(int logM) {
+  return logM - 6 < kPanelQueueLog ? logM - 6 : kPanelQueueLog;
+}
+// FP64 partials of a final step's launch (queue launch) with tile cfg.
+inline int64_t mass_partials(int cfg, const ContractArgs &a, bool queue) {
+  return cfg == kTileW && a.panel ? panel_partials(a, queue) : kPartialsPerTile * a.nblocks;
+}
 // Splits `count` floats (a multiple of 4) into `parts` bfloat16 planes of
 // `plane` elements each (the same split as the wide kernel's staging).
 Status launch_presplit(int parts, const float *src, void *dst, int64_t count, int64_t plane, hipStream_t s);

@@ -142,6 +142,7 @@ static Status tune_step(const NetLayout &L, size_t si, char *ws, const std::vect
     }
   }
   const Acc sa = step_acc(L.acc, st.wide_ok(), (int)st.S.size());
+  a.panel = sa == Acc::F32 && panel_step(p, si) && !od ? 1 : 0;
   const int64_t work = (int64_t(1) << (st.logM + st.logN)) * st.nbatch;
   const int reps = work >= (int64_t(1) << 24) ? 10 : 30;
   struct Events {  // destroyed on every return path
@@ -160,7 +161,7 @@ static Status tune_step(const NetLayout &L, size_t si, char *ws, const std::vect
     const TileShape sh = tile_shape(cfg);
     const int64_t M = int64_t(1) << st.logM, N = int64_t(1) << st.logN;
     // skip shapes that would leave most of every tile empty
-    if ((M < sh.bm || N < sh.bn) && cfg != kTileS && cfg != choose_tile(sa, a.nS, st.logM, st.logN, st.wide_ok(), st.nbatch)) continue;
+    if ((M < sh.bm || N < sh.bn) && cfg != kTileS && cfg != choose_tile(sa, a.nS, st.logM, st.logN, st.wide_ok(), a.panel != 0, st.nbatch)) continue;
     if (cfg == kTileW && !st.wide_ok()) continue;
     for (int xcd = 0; xcd < 2; ++xcd) {
       a.tilesM = (int)((M + sh.bm - 1) / sh.bm);

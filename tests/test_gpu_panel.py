@@ -1,0 +1,97 @@
+"""GPU parity of the panel contraction kernel (FP32 steps of three shared cuts,
+at least 2^22 outputs in a single call and 2^19 in a batch): panels and row
+runs at their smallest, live-term counts at and around the kernel's groups of
+eight, row flags read by the waves or through the label lists, batched
+intermediate steps, and the batched cross-entropy form.  Elementwise bound as in test_gpu_fd; sums in FP64 (n outputs of relative rounding 2^-53
+each leave at most n 2^-53 of the sum of magnitudes, 1e-12 here)."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import fd
+from tests.gpu_util import to_dev, oracle_inputs, abs_bound, elementwise_ok, U32
+
+pytestmark = pytest.mark.gpu
+cqc = pytest.importorskip("paper_2012_02333_amd")
+
+
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _entries(cut, seed, live):
+    """Random entries of which sub 0 keeps `live` rows (spread over all 64)."""
+    keep = set(np.linspace(0, 63, live).astype(int)) if live else set()
+    return W.random_entries(cut, seed=seed, zero_rows=[(0, r) for r in range(64) if r not in keep])
+
+
+def _check(cut, p, host, seed):
+    xs = W.sample_outputs(cut.n, 2048, seed=seed)
+    e64 = oracle_inputs(host)
+    got = p[torch.from_numpy(xs).to("cuda")].double().cpu().numpy()
+    ok, info = elementwise_ok(got, fd.reconstruct(e64, cut, xs), abs_bound(e64, cut, xs), U32, 4 ** cut.n_cuts)
+    assert ok, info
+
+
+@pytest.mark.parametrize("f,live", [((11, 11), 64), ((11, 11), 63), ((11, 11), 9), ((11, 11), 8), ((11, 11), 1),
+                                    ((11, 11), 0), ((6, 16), 64), ((6, 16), 37), ((16, 6), 64), ((16, 6), 21),
+                                    ((15, 8), 40)])
+def test_panel_step(f, live):
+    _gpu()
+    n = sum(f)
+    cut = W.CutMap(n, list(f), [0, 0, 0], [1, 1, 1], list(range(n)))
+    host, dev = to_dev(_entries(cut, 900 + live, live), torch.float32)
+    with cqc.trace() as tr:
+        p, mass = cqc.reconstruct_fd(dev, cqc.CutMap.from_workload(cut), precision="fp32")
+        torch.cuda.synchronize()
+    assert "wide_f32_final_panel" in tr.result, tr.result
+    _check(cut, p, host, 901)
+    s, sa = float(p.double().sum()), float(p.double().abs().sum())
+    assert abs(float(mass) - s) <= 1e-12 * sa
+    if live == 0:
+        assert sa == 0.0
+
+
+def test_panel_intermediate_and_final():
+    """A chain whose intermediate (64 batch entries, some without a live term) and final steps are panels."""
+    _gpu()
+    cut = W.CutMap(24, [8, 8, 8], [0, 0, 0, 1, 1, 1], [1, 1, 1, 2, 2, 2], list(range(24)))
+    ents = W.random_entries(cut, seed=910, zero_rows=[(1, r) for r in range(4096) if r % 64 in (3, 17, 62)])
+    host, dev = to_dev(ents, torch.float32)
+    with cqc.trace() as tr:
+        p, _ = cqc.reconstruct_fd(dev, cqc.CutMap.from_workload(cut), precision="fp32")
+        torch.cuda.synchronize()
+    assert "wide_f32_inter_panel" in tr.result and "wide_f32_final_panel" in tr.result, tr.result
+    _check(cut, p, host, 911)
+
+
+@pytest.mark.parametrize("keep", [True, False])
+@pytest.mark.parametrize("loss", [True, False])
+def test_panel_batch_xent(keep, loss):
+    """The cross-entropy form writes the two-pass gradient bit for bit; the
+    loss terms carry an FP32 logarithm (at most 2 ulp: 2^-22 of each term)."""
+    _gpu()
+    shapes = [((10, 10), 64), ((6, 13), 40), ((9, 10), 9), ((13, 7), 0)]
+    cuts_w = [W.CutMap(sum(f), list(f), [0, 0, 0], [1, 1, 1], list(range(sum(f)))) for f, _ in shapes]
+    dev = [to_dev([np.abs(E) for E in _entries(c, 920 + i, live)], torch.float32)[1]
+           for i, (c, (_, live)) in enumerate(zip(cuts_w, shapes))]
+    cuts = [cqc.CutMap.from_workload(c) for c in cuts_w]
+    t = [torch.from_numpy(W.dirichlet_target(c.n, 930 + i).astype(np.float32)).cuda() for i, c in enumerate(cuts_w)]
+    plain = cqc.Batch(dev, cuts, precision="fp32")
+    plain.run()
+    batch = cqc.Batch(dev, cuts, precision="fp32", targets=t, with_loss=loss, keep_outputs=keep)
+    for _ in range(2):
+        batch.run()
+    torch.cuda.synchronize()
+    for i in range(len(cuts)):
+        p = plain.outs[i]
+        assert torch.equal(batch.grads[i], cqc.xent_grad(p, t[i])), i
+        if keep:
+            assert torch.equal(batch.outs[i], p), i
+        if loss:
+            term = t[i].double() * p.double().clamp_min(1e-30).log()
+            assert abs(float(batch.losses[i]) + float(term.sum())) <= 2.0 ** -22 * float(term.abs().sum()), i
+        else:
+            assert abs(float(batch.mass[i]) - float(p.double().sum())) <= 1e-12 * float(p.double().abs().sum()), i
