@@ -286,7 +286,7 @@ __device__ __forceinline__ void contract_tile(const ContractArgs &a, uint32_t bl
     return;
   }
   if (a.partials) {
-    const double tot = wave_sum_f64(msum);
+    const double tot = xent_total<O, XE>(wave_sum_f64(msum));
     if (lane == 0) a.partials[kPartialsPerTile * blk + wave] = tot;
   }
 }
@@ -523,7 +523,7 @@ __device__ __forceinline__ void contract_small_tile(const ContractArgs &a, uint3
     return;
   }
   if (a.partials) {
-    const double tot = wave_sum_f64(msum);
+    const double tot = xent_total<O, XE>(wave_sum_f64(msum));
     if (lane == 0) a.partials[kPartialsPerTile * blk + wave] = tot;
   }
 }
@@ -554,10 +554,12 @@ __device__ __forceinline__ void contract_small_strip(const ContractArgs &a, uint
   const int rY = (int)(batch & ((1u << (2 * a.nRY)) - 1u));
   const int64_t M = int64_t(1) << a.logM, N = int64_t(1) << a.logN;
   const int64_t nw = (int64_t)tn * BN + wave * TN;
-  const float *X = static_cast<const float *>(a.X);
-  const float *Y = static_cast<const float *>(a.Y);
+  const gptr<const float> X = gbl(static_cast<const float *>(a.X));
+  const gptr<const float> Y = gbl(static_cast<const float *>(a.Y));
   const int l16 = lane & 15, lg = lane >> 4;
   const int nSv = 1 << (2 * a.nS);
+  // every load is made (rows past the term count read row 0) and the missing
+  // terms are zeroed afterwards: a masked load is a branch and a wait each
   int2 rrq[4];   // term 4q + lane/16 (rows -1: past the term count)
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -568,9 +570,9 @@ __device__ __forceinline__ void contract_small_strip(const ContractArgs &a, uint
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const bool kok = rrq[q].x >= 0;
-    const float *yr = Y + (int64_t)(kok ? rrq[q].y : 0) * N;
+    const gptr<const float> yr = Y + (int64_t)(kok ? rrq[q].y : 0) * N;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) ay[q][j] = kok ? yr[nw + j * 16 + l16] : 0.f;
+    for (int j = 0; j < 4; ++j) ay[q][j] = yr[nw + j * 16 + l16];
   }
   float bx[R][4][4];
   auto load_x = [&](int r) {
@@ -578,15 +580,21 @@ __device__ __forceinline__ void contract_small_strip(const ContractArgs &a, uint
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const bool kok = rrq[q].x >= 0;
-      const float *xr = X + (int64_t)(kok ? rrq[q].x : 0) * M;
+      const gptr<const float> xr = X + (int64_t)(kok ? rrq[q].x : 0) * M;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) bx[r][i][q] = kok ? xr[mw + i * 16 + l16] : 0.f;
+      for (int i = 0; i < 4; ++i) bx[r][i][q] = xr[mw + i * 16 + l16];
     }
   };
   load_x(0);
+  if (nSv < 16) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) ay[q][j] = rrq[q].x >= 0 ? ay[q][j] : 0.f;
+  }
   float *st = stage + wave * 16 * SLD;
   const float sc = MODE == kModeIntermediate ? 1.0f : (float)a.scale;
-  O *Zb = MODE == kModeIntermediate ? static_cast<O *>(a.Z) + (int64_t)batch * M * N : static_cast<O *>(a.Z);
+  const gptr<O> Zb = gbl(static_cast<O *>(a.Z)) + (MODE == kModeIntermediate ? (int64_t)batch * M * N : 0);
   // cross-entropy form: the targets of a whole tile, loaded before its first
   // store (strips cover whole tiles)
   f32x4 tv[XE ? 16 : 1];
@@ -625,7 +633,7 @@ __device__ __forceinline__ void contract_small_strip(const ContractArgs &a, uint
           xent_emit4(a, (mw + i * 16 + row) * N + nw + col, w, tv[XE ? 4 * i + rr / 4 : 0], c, XE == 2);
           msum += (c[0] + c[1]) + (c[2] + c[3]);
         } else {
-          *reinterpret_cast<float4 *>(Zb + (mw + i * 16 + row) * N + nw + col) = v;
+          *(gptr<f32x4>)(Zb + (mw + i * 16 + row) * N + nw + col) = f32x4{v.x, v.y, v.z, v.w};
           if (MODE != kModeIntermediate) msum += ((double)v.x + (double)v.y) + ((double)v.z + (double)v.w);
         }
       }
@@ -634,7 +642,7 @@ __device__ __forceinline__ void contract_small_strip(const ContractArgs &a, uint
     if (MODE == kModeIntermediate) {
       if (a.flagZ && tm == 0 && tn == 0 && tid == 0) a.flagZ[batch] = nSv > 0;
     } else if (a.partials) {
-      const double tot = wave_sum_f64(msum);
+      const double tot = xent_total<O, XE>(wave_sum_f64(msum));
       const int64_t tile = (int64_t)batch * a.tilesM * a.tilesN + (int64_t)tm * tilesN + tn;
       if (lane == 0) a.partials[kPartialsPerTile * tile + wave] = tot;
     }

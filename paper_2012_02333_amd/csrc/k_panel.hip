@@ -244,7 +244,7 @@ __device__ __forceinline__ void panel_unit(const ContractArgs &a, int lt, int64_
   const double s = pt.cnt == kPT ? panel_rows<MODE, XE, true>(a, pt, batch, run << (lt + 6), 1 << lt, n0)
                                  : panel_rows<MODE, XE, false>(a, pt, batch, run << (lt + 6), 1 << lt, n0);
   if (MODE != kModeIntermediate && a.partials) {
-    const double tot = wave_sum_f64(s);
+    const double tot = xent_total<float, XE>(wave_sum_f64(s));
     if ((threadIdx.x & 63) == 0) gbl(a.partials)[unit] = tot;
   }
 }

@@ -597,7 +597,7 @@ __device__ __forceinline__ void wide_run(Seq &seq) {
     }
     double *partials = uni(a.partials);
     if (MODE != kModeIntermediate && partials) {
-      const double tot = wave_sum_f64(msum);
+      const double tot = xent_total<O, XE>(wave_sum_f64(msum));
       if (lane == 0) gbl(partials)[kPartialsPerTile * t.blk + wave] = tot;
     }
   };

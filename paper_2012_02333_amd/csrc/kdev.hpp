@@ -117,6 +117,12 @@ template <> __device__ __forceinline__ void store4<double>(double *p, const doub
 // to p_x: -t_x / p_x above the floor, 0 at or below it (flat there).  The floor
 // test is made on p widened to FP64, the division in T.
 constexpr double kXentFloor = 1e-30;
+// The test for FP32 p without widening: (float)1e-30 is the smallest float
+// above 1e-30, so (double)p > 1e-30 exactly if p >= (float)1e-30.
+constexpr float kXentFloorF = 1e-30f;
+static_assert((double)kXentFloorF > kXentFloor, "the nearest float lies above the floor");
+__device__ __forceinline__ bool xent_above(float p) { return p >= kXentFloorF; }
+__device__ __forceinline__ bool xent_above(double p) { return p > kXentFloor; }
 template <typename T>
 __device__ __forceinline__ T xent_grad_of(T p, T t) {
   // divided first and selected afterwards: as a conditional division the
@@ -124,32 +130,38 @@ __device__ __forceinline__ T xent_grad_of(T p, T t) {
   // being scheduled around their loads and stores
   T q = -t / p;
   asm volatile("" : "+v"(q));
-  return (double)p > kXentFloor ? q : T(0);
+  return xent_above(p) ? q : T(0);
 }
 
 // Partial-sum contribution of one output p of a cross-entropy final step
-// (ContractArgs::xt): the loss term -t log max(p, 1e-30) when the loss is
-// asked for, else p itself (the mass).  The logarithm is taken in the output
-// precision (FP32 outputs: an FP32 logarithm, relative error about 1e-7 per
-// term, no larger than what FP32 rounding of p itself leaves in the term;
-// the FP64 logarithm is several times the code of the whole store path and
-// keeps the epilogues from being unrolled); terms are summed in FP64.
-__device__ __forceinline__ double xent_log_floor(float p) {
-  return (double)logf((double)p > kXentFloor ? p : (float)kXentFloor);
-}
+// (ContractArgs::xt): the loss term -t log max(p, 1e-30) in units of
+// xent_unit, when the loss is asked for, else p itself (the mass).  FP32
+// outputs take the base-2 logarithm in FP32 (one instruction, one ulp - no
+// larger than what FP32 rounding of p itself leaves in the term) and FP64 sums
+// of FP64 products; ln 2 multiplies a wave's sum once, in FP64.  Next to a
+// float epilogue per output this is a third of the instructions of logf, whose
+// rounding to FP32 it also saves.
+__device__ __forceinline__ double xent_log_floor(float p) { return (double)__builtin_amdgcn_logf(fmaxf(p, kXentFloorF)); }
 __device__ __forceinline__ double xent_log_floor(double p) { return log(p > kXentFloor ? p : kXentFloor); }
+template <typename T> struct XentUnit { static constexpr double kLoss = 1.0; };
+template <> struct XentUnit<float> { static constexpr double kLoss = 0.69314718055994530942; };
 template <typename T>
 __device__ __forceinline__ double xent_part(T p, T t, bool loss) {
   return loss ? -(double)t * xent_log_floor(p) : (double)p;
+}
+// A wave's sum of contributions as it goes into the partials.
+template <typename T, int XE>
+__device__ __forceinline__ double xent_total(double sum) {
+  return XE == 2 ? sum * XentUnit<T>::kLoss : sum;
 }
 
 // One output p of a cross-entropy final step at element o of the output order:
 // gradient to xg, p to z if set; returns the partial-sum contribution.
 template <typename T>
 __device__ __forceinline__ double xent_put1(const ContractArgs &a, int64_t o, T p, bool loss) {
-  const T t = static_cast<const T *>(a.xt)[o];
-  if (a.Z) static_cast<T *>(a.Z)[o] = p;
-  static_cast<T *>(a.xg)[o] = xent_grad_of(p, t);
+  const T t = gbl(static_cast<const T *>(a.xt))[o];
+  if (a.Z) gbl(static_cast<T *>(a.Z))[o] = p;
+  gbl(static_cast<T *>(a.xg))[o] = xent_grad_of(p, t);
   return xent_part(p, t, loss);
 }
 
@@ -175,15 +187,15 @@ __device__ __forceinline__ void xent_put4(const ContractArgs &a, int64_t o, cons
 // a whole tile before its first store instead.  Targets are read once and
 // gradients written once: non-temporal accesses.
 __device__ __forceinline__ f32x4 xent_t4(const ContractArgs &a, int64_t o) {
-  return __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(static_cast<const float *>(a.xt) + o));
+  return __builtin_nontemporal_load((gptr<const f32x4>)(gbl(static_cast<const float *>(a.xt)) + o));
 }
 __device__ __forceinline__ void xent_emit4(const ContractArgs &a, int64_t o, const float (&v)[4], const f32x4 &t,
                                            double (&c)[4], bool loss) {
-  if (a.Z) store4<float>(static_cast<float *>(a.Z) + o, v);
+  if (a.Z) *(gptr<f32x4>)(gbl(static_cast<float *>(a.Z)) + o) = f32x4{v[0], v[1], v[2], v[3]};
   f32x4 g;
 #pragma unroll
   for (int r = 0; r < 4; ++r) g[r] = xent_grad_of(v[r], t[r]);
-  __builtin_nontemporal_store(g, reinterpret_cast<f32x4 *>(static_cast<float *>(a.xg) + o));
+  __builtin_nontemporal_store(g, (gptr<f32x4>)(gbl(static_cast<float *>(a.xg)) + o));
 #pragma unroll
   for (int r = 0; r < 4; ++r) c[r] = xent_part(v[r], t[r], loss);
 }
