@@ -41,7 +41,7 @@ struct BatchBuild {
   std::vector<MassDesc> mass;
   struct G {
     int level, mode, cfg;
-    bool small, strip, panel;
+    bool small, strip, panel, stream;
     int xent;
     Acc acc;
     std::vector<std::pair<double, ContractArgs>> steps;  // (cost, args)
@@ -210,7 +210,7 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
       if (strip) a.flagX = a.flagY = nullptr;
       // cross-entropy form of the final step: 1 gradient, 2 gradient and loss
       const int xe = xent == nullptr || !last ? 0 : (xent->losses && xent->losses[i] ? 2 : 1);
-      auto key = std::make_tuple(level, (int)a.mode, cfg, (int)small * 2 + (int)(strip || a.panel), (int)sa, xe);
+      auto key = std::make_tuple(level, (int)a.mode, cfg, (int)small * 2 + (int)(strip || a.panel), (int)sa + (a.panel && a.nS > 3 ? 64 : 0), xe);
       auto it = gidx.find(key);
       if (it == gidx.end()) {
         it = gidx.emplace(key, B.groups.size()).first;
@@ -221,6 +221,7 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
         g.small = small;
         g.strip = strip;
         g.panel = a.panel != 0;
+        g.stream = a.panel && a.nS > 3;
         g.xent = xe;
         g.acc = sa;
         B.groups.push_back(g);
@@ -294,6 +295,7 @@ static Status batch_run(cqc_batch_s *b, hipStream_t s) {
     q.btotal = G.btotal;
     q.xent = G.xent;
     q.panel = G.panel;
+    q.stream = G.stream;
     if (G.strip) CQC_TRY(launch_contract_strip_queue(G.mode, q, s));
     else CQC_TRY(launch_contract_queue(G.acc, G.mode, G.cfg, G.small, q, s));
   }
@@ -353,6 +355,7 @@ static Status batch_create(const cqc_instance *inst, int32_t n_inst, cqc_dtype i
     bg.small = G.small;
     bg.strip = G.strip;
     bg.panel = G.panel;
+    bg.stream = G.stream;
     bg.xent = G.xent;
     bg.acc = G.acc;
     bg.descs = reinterpret_cast<const ContractArgs *>(ws + B.desc_off[g]);

@@ -22,7 +22,8 @@ struct cqc_batch_s {
     int level, mode, cfg;
     bool small;
     bool strip;     // two-tile strips of the FP32 small-term kernel
-    bool panel;     // wide steps of the panel kernel
+    bool panel;     // wide steps of the panel kernels
+    bool stream;    //   with more than three shared cuts
     int xent;       // final steps of the cross-entropy form: 1 gradient, 2 gradient and loss
     cqc::Acc acc;   // arithmetic of the group's steps
     const cqc::ContractArgs *descs;

@@ -278,6 +278,151 @@ void k_panel_queue(const ContractArgs *__restrict__ descs, const int64_t *__rest
   }
 }
 
+// ---------------------------------------------------------------------------
+// Four and more shared cuts: the terms of a panel no longer fit the registers,
+// so both operands stream.  A wave owns one 64 x 64 output tile; every term is
+// one load of each operand (64 columns from a scalar row offset) and two
+// products of 64 rows by 32 columns (even columns, odd columns), 128
+// matrix-core cycles; kST terms of both are in flight, and the 2 x 2 waves of
+// a block share their rows in L1.  No LDS and no barrier: three waves per SIMD
+// cover each other's first loads and last stores.  The staged wide kernel
+// spent as long staging, waiting at two barriers per 32 terms and on its
+// epilogue as on its products: 88.7 M outputs of 256 terms with the
+// cross-entropy epilogue 599 us there, 470 us here (two or three waves per SIMD
+// alike; products alone about 300); a single 2^22-output step 45 us, 28 here.
+constexpr int kST = 32;
+
+// Waves of a block over a step's tiles: 2 x 2, or in a line where one operand
+// is a single tile wide.
+struct StreamShape {
+  int wm, wn, tm, tn;   // log2 of waves and of block tiles, rows and columns
+};
+__host__ __device__ inline StreamShape stream_shape(int logM, int logN) {
+  const int m = logM - 6, n = logN - 6;
+  StreamShape s;
+  s.wn = n < 1 ? 0 : m == 0 && n > 1 ? 2 : 1;
+  s.wm = m < 2 - s.wn ? m : 2 - s.wn;
+  s.tm = m - s.wm;
+  s.tn = n - s.wn;
+  return s;
+}
+
+template <int MODE, int XE>
+__device__ __forceinline__ void stream_block(const ContractArgs &a, int64_t blk) {
+  const int lane = threadIdx.x & 63, wave = uni((int32_t)(threadIdx.x >> 6));
+  const int logM = uni(a.logM), logN = uni(a.logN);
+  const StreamShape sh = stream_shape(logM, logN);
+  const int64_t part = 4 * blk + wave;
+  if (wave >> (sh.wm + sh.wn)) {
+    if (MODE != kModeIntermediate && a.partials && lane == 0) gbl(a.partials)[part] = 0.0;
+    return;
+  }
+  const int64_t tn = blk & ((int64_t(1) << sh.tn) - 1), tm = (blk >> sh.tn) & ((int64_t(1) << sh.tm) - 1);
+  const int64_t batch = blk >> (sh.tn + sh.tm);
+  const int64_t m0 = ((tm << sh.wm) + (wave >> sh.wn)) * kPT;
+  const int64_t n0 = ((tn << sh.wn) + (wave & ((1 << sh.wn) - 1))) * kPT;
+  const int cnt = cst(uni(a.counts))[batch];
+  const int32_t ld = uni(a.list_ld);
+  const cptr<uint32_t> offX = cst(reinterpret_cast<const uint32_t *>(uni(a.lists))) + batch * 2 * ld;
+  const cptr<uint32_t> offY = offX + ld;
+  const BufRsrc X = buf_rsrc(uni(a.X), 4u << (logM + 2 * (uni(a.nS) + uni(a.nRX))));
+  const BufRsrc Y = buf_rsrc(uni(a.Y), 4u << (logN + 2 * (uni(a.nS) + uni(a.nRY))));
+  const uint32_t xl = 4u * lane, mb = 4u * (uint32_t)m0, nb = 4u * (uint32_t)n0;
+  const uint32_t yl = 4u * (lane < 32 ? 2 * lane : 2 * lane - 63);   // even columns, then odd ones
+  // groups of kST terms (at least one; the lists are padded with offset 0)
+  const int groups = cnt == 0 ? 1 : (cnt + kST - 1) / kST;
+  float x[kST], y[kST];
+#pragma unroll
+  for (int t = 0; t < kST; ++t) {
+    x[t] = buf_load(X, xl, offX[t] + mb);
+    y[t] = buf_load(Y, yl, offY[t] + nb);
+  }
+  f32x32 acc0{}, acc1{};
+  for (int g = 0; g + 1 < groups; ++g) {
+    const cptr<uint32_t> nx = offX + (g + 1) * kST, ny = offY + (g + 1) * kST;
+#pragma unroll
+    for (int t = 0; t < kST; ++t) {
+      acc0 = __builtin_amdgcn_mfma_f32_32x32x1f32(x[t], y[t], acc0, 0, 0, 1);
+      acc1 = __builtin_amdgcn_mfma_f32_32x32x1f32(x[t], y[t], acc1, 0, 0, 2);
+      x[t] = buf_load(X, xl, nx[t] + mb);
+      y[t] = buf_load(Y, yl, ny[t] + nb);
+      if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  // the tile's outputs: 256 contiguous bytes of two rows per access
+  const uint32_t zl = 4u * (((uint32_t)(lane >> 5) << (logN + 2)) + 2u * (lane & 31));
+  auto rows = [&](const void *base) {
+    return buf_rsrc(static_cast<const char *>(base) + ((MODE == kModeIntermediate ? batch << (logM + logN) : 0) +
+                                                       (m0 << logN) + n0) * 4, base ? 256u << logN : 0u);
+  };
+  auto row_off = [&](int r) { return (uint32_t)(4 * (32 * (r / 16) + (r % 4) + 8 * ((r % 16) / 4))) << logN; };
+  // cross-entropy form: half the targets before the last group, the others as
+  // the first are used
+  constexpr int kTv = 16;
+  f32x2 tv[XE ? kTv : 1];
+  const BufRsrc T = rows(XE ? uni(a.xt) : nullptr);
+  if constexpr (XE)
+#pragma unroll
+    for (int r = 0; r < kTv; ++r) tv[r] = buf_load2_nt(T, zl, row_off(r));
+  const int rest = cnt - (groups - 1) * kST;   // terms of the last group
+#pragma unroll
+  for (int t = 0; t < kST; ++t) {
+    const float xv = t < rest ? x[t] : 0.f, yv = t < rest ? y[t] : 0.f;
+    acc0 = __builtin_amdgcn_mfma_f32_32x32x1f32(xv, yv, acc0, 0, 0, 1);
+    acc1 = __builtin_amdgcn_mfma_f32_32x32x1f32(xv, yv, acc1, 0, 0, 2);
+  }
+  const float sc = MODE == kModeIntermediate ? 1.f : (float)uni(a.scale);
+  const BufRsrc Z = rows(uni(a.Z)), G = rows(XE ? uni(a.xg) : nullptr);
+  double msum = 0.0;
+#pragma unroll
+  for (int r = 0; r < 32; ++r) {
+    const float v0 = acc0[r] * sc, v1 = acc1[r] * sc;
+    if (MODE == kModeIntermediate || !XE) buf_store2_nt(v0, v1, Z, zl, row_off(r));
+    if constexpr (XE) {
+      const f32x2 t = tv[r % kTv];
+      if (r + kTv < 32) tv[r % kTv] = buf_load2_nt(T, zl, row_off(r + kTv));
+      buf_store2_nt(v0, v1, Z, zl, row_off(r));   // dropped where p is not kept
+      buf_store2_nt(xent_grad_of(v0, t[0]), xent_grad_of(v1, t[1]), G, zl, row_off(r));
+      msum += xent_part(v0, t[0], XE == 2) + xent_part(v1, t[1], XE == 2);
+    } else if (MODE != kModeIntermediate) {
+      msum += (double)v0 + (double)v1;
+    }
+  }
+  if (MODE != kModeIntermediate && a.partials) {
+    const double tot = xent_total<float, XE>(wave_sum_f64(msum));
+    if (lane == 0) gbl(a.partials)[part] = tot;
+  }
+}
+
+template <int MODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
+void k_stream(const ContractArgs a) {
+  if (gated_off(a.gate, a.gate_val)) return;
+  // blocks of one XCD take a contiguous range of tiles: they share operand rows in L2
+  stream_block<MODE, 0>(a, a.xcd_remap ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x);
+}
+
+template <int MODE, int XE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
+void k_stream_queue(const ContractArgs *__restrict__ descs, const int64_t *__restrict__ prefix, int ndesc,
+                    unsigned long long *queue, int64_t total) {
+  __shared__ int64_t item;
+  for (;;) {
+    __syncthreads();
+    if (threadIdx.x == 0) item = (int64_t)atomicAdd(queue, 1ull);
+    __syncthreads();
+    const int64_t it = uni(item);
+    if (it >= total) return;
+    const int d = uni(find_desc(prefix, ndesc, it));
+    stream_block<MODE, XE>(descs[d], it - uni(prefix[d]));
+  }
+}
+
+static int64_t stream_blocks(const ContractArgs &a) {
+  const StreamShape sh = stream_shape(a.logM, a.logN);
+  return a.nbatch << (sh.tm + sh.tn);
+}
+
 // Row tiles per unit (log2) of a single-step launch: about 16384 units.
 static int panel_log_tiles(const ContractArgs &a) {
   const int total = a.logM + a.logN - 12 + 2 * (a.nRX + a.nRY);   // log2 of 64 x 64 tiles
@@ -285,6 +430,7 @@ static int panel_log_tiles(const ContractArgs &a) {
 }
 
 int64_t panel_partials(const ContractArgs &a, bool queue) {
+  if (a.nS > 3) return 4 * stream_blocks(a);
   return a.nbatch << (a.logM + a.logN - 12 - (queue ? panel_queue_log_tiles(a.logM) : panel_log_tiles(a)));
 }
 
@@ -295,8 +441,14 @@ constexpr int kPanelFlags = 8;
 
 Status launch_panel(const ContractArgs &args, hipStream_t s) {
   ContractArgs a = args;
-  if (a.nS != 3 || a.logM < 6 || a.logN < 6 || a.mode == kModeFinalDeposit)
+  if (a.nS < 3 || a.logM < 6 || a.logN < 6 || a.mode == kModeFinalDeposit)
     return Status::fail(CQC_ERR_INVALID_ARG, "panel contraction: step shape");
+  if (a.nS > 3) {
+    CQC_TRY(launch_label_list(a, s));
+    const dim3 g((unsigned)stream_blocks(a)), b(256);
+    return a.mode == kModeIntermediate ? launch("wide_f32_inter_stream", k_stream<kModeIntermediate>, g, b, 0, s, a)
+                                       : launch("wide_f32_final_stream", k_stream<kModeFinalBlocked>, g, b, 0, s, a);
+  }
   if (a.flagX && a.nchX + a.nchY > kPanelFlags) CQC_TRY(launch_label_list(a, s));
   else a.lists = nullptr;
   const int lt = panel_log_tiles(a);
@@ -311,6 +463,16 @@ Status launch_panel_queue(int mode, const QueueLaunch &q, hipStream_t s) {
   const dim3 grid(q.grid), block(256);
   CQC_TRY(launch_label_list_table(q, s));
   const char *nm = "wide_f32_queue", *nx = "wide_f32_queue_xent";
+  if (q.stream) {
+    if (mode == kModeIntermediate)
+      return launch(nm, k_stream_queue<kModeIntermediate, 0>, grid, block, 0, s, q.descs, q.prefix, q.ndesc, q.queue, q.total);
+    if (mode != kModeFinalBlocked) return Status::fail(CQC_ERR_INVALID_ARG, "panel queue: output mode");
+    if (q.xent == 2)
+      return launch(nx, k_stream_queue<kModeFinalBlocked, 2>, grid, block, 0, s, q.descs, q.prefix, q.ndesc, q.queue, q.total);
+    if (q.xent == 1)
+      return launch(nx, k_stream_queue<kModeFinalBlocked, 1>, grid, block, 0, s, q.descs, q.prefix, q.ndesc, q.queue, q.total);
+    return launch(nm, k_stream_queue<kModeFinalBlocked, 0>, grid, block, 0, s, q.descs, q.prefix, q.ndesc, q.queue, q.total);
+  }
   if (mode == kModeIntermediate)
     return launch(nm, k_panel_queue<kModeIntermediate, 0>, grid, block, 0, s, q.descs, q.prefix, q.ndesc, q.queue, q.total);
   if (mode != kModeFinalBlocked) return Status::fail(CQC_ERR_INVALID_ARG, "panel queue: output mode");

@@ -164,7 +164,8 @@ struct QueueLaunch {
   uint32_t grid;
   const int64_t *bprefix;  // wide kernel: bprefix[d] = first batch entry of step d over the table
   int64_t btotal;          //   and the total (one label-list block per batch entry)
-  bool panel = false;      // wide steps of the panel kernel
+  bool panel = false;      // wide steps of the panel kernels
+  bool stream = false;     //   with more than three shared cuts
   int xent = 0;            // final steps of the cross-entropy form (ContractArgs::xt):
                            //   1 gradient (partials sum p), 2 gradient and loss
 };
@@ -191,10 +192,10 @@ Status launch_contract_wide(int parts, bool out_double, const ContractArgs &a, h
 // and panel kernels.
 Status launch_label_list(const ContractArgs &a, hipStream_t s);
 Status launch_label_list_table(const QueueLaunch &q, hipStream_t s);
-// Panel kernel (k_panel.hip): the wide steps with ContractArgs::panel set.
+// Panel kernels (k_panel.hip): the wide steps with ContractArgs::panel set.
 Status launch_panel(const ContractArgs &a, hipStream_t s);
 Status launch_panel_queue(int mode, const QueueLaunch &q, hipStream_t s);
-// Its units: four per block or queue item, one FP64 partial each in a final step.
+// Their waves: four per block or queue item, one FP64 partial each in a final step.
 int64_t panel_partials(const ContractArgs &a, bool queue);
 // Row tiles per unit (log2) of a queue launch: at most 2^kPanelQueueLog, so that
 // a step of 2^19 outputs still gives 32 waves and large ones reload a panel

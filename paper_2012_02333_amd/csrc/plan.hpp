@@ -57,10 +57,10 @@ struct Step {
     return 2 * (S.size() + RX.size()) + logM <= 30 && 2 * (S.size() + RY.size()) + logN <= 30 && logM >= 1 &&
            logN >= 1;
   }
-  // the panel kernel: three shared cuts, whole 64 x 64 tiles, and operands and
-  // 32 output rows within 2^31 bytes
+  // the panel kernels: three and more shared cuts, whole 64 x 64 tiles, and
+  // operands and 64 output rows within 2^31 bytes
   bool panel_ok() const {
-    return S.size() == 3 && logM >= 6 && logN >= 6 && logN <= 23 && 2 * (S.size() + RX.size()) + logM <= 29 &&
+    return S.size() >= 3 && logM >= 6 && logN >= 6 && logN <= 23 && 2 * (S.size() + RX.size()) + logM <= 29 &&
            2 * (S.size() + RY.size()) + logN <= 29;
   }
 };

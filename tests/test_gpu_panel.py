@@ -1,5 +1,5 @@
-"""GPU parity of the panel contraction kernel (FP32 steps of three shared cuts,
-at least 2^22 outputs in a single call and 2^19 in a batch): panels and row
+"""GPU parity of the panel contraction kernels (FP32 steps of three shared cuts
+in registers, of four and more streamed; at least 2^22 outputs in a single call and 2^19 in a batch): panels and row
 runs at their smallest, live-term counts at and around the kernel's groups of
 eight, row flags read by the waves or through the label lists, batched
 intermediate steps, and the batched cross-entropy form.  Elementwise bound as in test_gpu_fd; sums in FP64 (n outputs of relative rounding 2^-53
@@ -22,9 +22,10 @@ def _gpu():
 
 
 def _entries(cut, seed, live):
-    """Random entries of which sub 0 keeps `live` rows (spread over all 64)."""
-    keep = set(np.linspace(0, 63, live).astype(int)) if live else set()
-    return W.random_entries(cut, seed=seed, zero_rows=[(0, r) for r in range(64) if r not in keep])
+    """Random entries of which sub 0 keeps `live` rows (spread over all of them)."""
+    rows = cut.entry_shape(0)[0]
+    keep = set(np.linspace(0, rows - 1, live).astype(int)) if live else set()
+    return W.random_entries(cut, seed=seed, zero_rows=[(0, r) for r in range(rows) if r not in keep])
 
 
 def _check(cut, p, host, seed):
@@ -54,6 +55,26 @@ def test_panel_step(f, live):
         assert sa == 0.0
 
 
+@pytest.mark.parametrize("f,k,live", [((11, 11), 4, 256), ((11, 11), 4, 33), ((11, 11), 4, 32), ((11, 11), 4, 31),
+                                      ((11, 11), 4, 1), ((11, 11), 4, 0), ((6, 16), 4, 100), ((16, 6), 4, 64),
+                                      ((15, 7), 4, 200), ((11, 11), 5, 1000)])
+def test_stream_step(f, k, live):
+    """Four and five shared cuts: the streamed form, with one panel or one row tile at its narrowest."""
+    _gpu()
+    n = sum(f)
+    cut = W.CutMap(n, list(f), [0] * k, [1] * k, list(range(n)))
+    host, dev = to_dev(_entries(cut, 940 + live, live), torch.float32)
+    with cqc.trace() as tr:
+        p, mass = cqc.reconstruct_fd(dev, cqc.CutMap.from_workload(cut), precision="fp32")
+        torch.cuda.synchronize()
+    assert "wide_f32_final_stream" in tr.result, tr.result
+    _check(cut, p, host, 941)
+    s, sa = float(p.double().sum()), float(p.double().abs().sum())
+    assert abs(float(mass) - s) <= 1e-12 * sa
+    if live == 0:
+        assert sa == 0.0
+
+
 def test_panel_intermediate_and_final():
     """A chain whose intermediate (64 batch entries, some without a live term) and final steps are panels."""
     _gpu()
@@ -73,10 +94,11 @@ def test_panel_batch_xent(keep, loss):
     """The cross-entropy form writes the two-pass gradient bit for bit; the
     loss terms carry an FP32 logarithm (at most 2 ulp: 2^-22 of each term)."""
     _gpu()
-    shapes = [((10, 10), 64), ((6, 13), 40), ((9, 10), 9), ((13, 7), 0)]
-    cuts_w = [W.CutMap(sum(f), list(f), [0, 0, 0], [1, 1, 1], list(range(sum(f)))) for f, _ in shapes]
+    shapes = [((10, 10), 3, 64), ((6, 13), 3, 40), ((9, 10), 3, 9), ((13, 7), 3, 0),
+              ((10, 10), 4, 256), ((6, 13), 4, 65), ((13, 6), 4, 0)]
+    cuts_w = [W.CutMap(sum(f), list(f), [0] * k, [1] * k, list(range(sum(f)))) for f, k, _ in shapes]
     dev = [to_dev([np.abs(E) for E in _entries(c, 920 + i, live)], torch.float32)[1]
-           for i, (c, (_, live)) in enumerate(zip(cuts_w, shapes))]
+           for i, (c, (_, _, live)) in enumerate(zip(cuts_w, shapes))]
     cuts = [cqc.CutMap.from_workload(c) for c in cuts_w]
     t = [torch.from_numpy(W.dirichlet_target(c.n, 930 + i).astype(np.float32)).cuda() for i, c in enumerate(cuts_w)]
     plain = cqc.Batch(dev, cuts, precision="fp32")
