@@ -41,7 +41,8 @@ struct BatchBuild {
   std::vector<MassDesc> mass;
   struct G {
     int level, mode, cfg;
-    bool small, strip, panel, stream;
+    bool small, panel, stream;
+    int rows, nS;
     int xent;
     Acc acc;
     std::vector<std::pair<double, ContractArgs>> steps;  // (cost, args)
@@ -159,6 +160,7 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
       a.nblocks = (int64_t)a.tilesM * a.tilesN * st.nbatch;
       a.mx = to_dev(st.mx);
       a.my = to_dev(st.my);
+      a.rows = rows_cols(step_acc(B.acc, st.wide_ok(), a.nS), step_mode, cfg, a.nS, st.logM, st.logN);
       set_lists(L, s, ws, &a);
       const Acc sa = step_acc(B.acc, st.wide_ok(), (int)st.S.size());
       a.panel = cfg == kTileW && sa == Acc::F32 && panel_step(p, s) ? 1 : 0;
@@ -201,16 +203,10 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
         }
       }
       const bool small = a.nS <= 2;
-      // FP32 small-term steps over whole 64 x 256 tiles in pairs of rows run as
-      // two-tile strips with every term kept (dead terms add exact zeros) -
-      // for instances whose one-instance call computes no row flags, so the
-      // outputs stay bitwise those of that call
-      const bool strip = small && sa == Acc::F32 && cfg == kTileL && st.logM >= 7 && st.logN >= 8 &&
-                         (a.mode == kModeFinalBlocked || a.mode == kModeIntermediate) && !inst_flags;
-      if (strip) a.flagX = a.flagY = nullptr;
       // cross-entropy form of the final step: 1 gradient, 2 gradient and loss
       const int xe = xent == nullptr || !last ? 0 : (xent->losses && xent->losses[i] ? 2 : 1);
-      auto key = std::make_tuple(level, (int)a.mode, cfg, (int)small * 2 + (int)(strip || a.panel), (int)sa + (a.panel && a.nS > 3 ? 64 : 0), xe);
+      auto key = std::make_tuple(level, (int)a.mode, cfg, (int)small * 2 + a.panel + 64 * (a.rows ? 4 * a.rows + a.nS : 0),
+                                 (int)sa + (a.panel && a.nS > 3 ? 64 : 0), xe);
       auto it = gidx.find(key);
       if (it == gidx.end()) {
         it = gidx.emplace(key, B.groups.size()).first;
@@ -219,7 +215,8 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
         g.mode = a.mode;
         g.cfg = cfg;
         g.small = small;
-        g.strip = strip;
+        g.rows = a.rows;
+        g.nS = a.nS;
         g.panel = a.panel != 0;
         g.stream = a.panel && a.nS > 3;
         g.xent = xe;
@@ -296,7 +293,7 @@ static Status batch_run(cqc_batch_s *b, hipStream_t s) {
     q.xent = G.xent;
     q.panel = G.panel;
     q.stream = G.stream;
-    if (G.strip) CQC_TRY(launch_contract_strip_queue(G.mode, q, s));
+    if (G.rows) CQC_TRY(launch_rows_table(G.mode, G.rows, G.nS, q, s));
     else CQC_TRY(launch_contract_queue(G.acc, G.mode, G.cfg, G.small, q, s));
   }
   if (b->n_mass > 0) CQC_TRY(launch_mass_table(b->mass_descs, b->n_mass, s));
@@ -340,7 +337,7 @@ static Status batch_create(const cqc_instance *inst, int32_t n_inst, cqc_dtype i
       descs.push_back(st.second);
       const int64_t nb = st.second.nblocks;
       prefix.push_back(prefix.back() + (G.panel ? (panel_partials(st.second, true) + 3) / 4
-                                        : G.strip ? nb / kStripRows
+                                        : G.rows  ? (rows_units(st.second) + 3) / 4
                                         : G.small ? (nb + kSmallTilesPerItem - 1) / kSmallTilesPerItem
                                                   : nb));
       bprefix.push_back(bprefix.back() + st.second.nbatch);
@@ -353,7 +350,8 @@ static Status batch_create(const cqc_instance *inst, int32_t n_inst, cqc_dtype i
     bg.mode = G.mode;
     bg.cfg = G.cfg;
     bg.small = G.small;
-    bg.strip = G.strip;
+    bg.rows = G.rows;
+    bg.nS = G.nS;
     bg.panel = G.panel;
     bg.stream = G.stream;
     bg.xent = G.xent;

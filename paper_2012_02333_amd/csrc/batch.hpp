@@ -21,7 +21,7 @@ struct cqc_batch_s {
   struct Group {
     int level, mode, cfg;
     bool small;
-    bool strip;     // two-tile strips of the FP32 small-term kernel
+    int rows, nS;   // small-term steps of the row kernel: columns per lane and shared cuts
     bool panel;     // wide steps of the panel kernels
     bool stream;    //   with more than three shared cuts
     int xent;       // final steps of the cross-entropy form: 1 gradient, 2 gradient and loss

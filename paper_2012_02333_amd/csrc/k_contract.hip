@@ -528,150 +528,6 @@ __device__ __forceinline__ void contract_small_tile(const ContractArgs &a, uint3
   }
 }
 
-
-// Two-tile strips for the 64 x 256 FP32 tile with FP32 output and every term
-// kept (no row flags): a block takes two vertically adjacent tiles, loads the Y operands
-// once and issues the X loads of the second tile before the first tile's
-// output stores, so that wait never covers stores.  Half as many blocks
-// start together, which spreads the operand fetch at the start of the launch
-// over the first tile's stores.  One partial mass per tile, as in the
-// one-tile kernel.
-
-template <typename O, int MODE, int XE = 0>
-__device__ __forceinline__ void contract_small_strip(const ContractArgs &a, uint32_t strip) {
-  static_assert(sizeof(O) == 4, "staged float4 stores: FP32 output only");
-  constexpr int R = kStripRows, BM = 64, BN = 256, TN = 64, SLD = TN + 4;
-  using Op = MfmaOp<float>;
-  using V = typename Op::V;
-  __shared__ float stage[4 * 16 * SLD];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint32_t tilesN = (uint32_t)a.tilesN, groups = (uint32_t)a.tilesM / R;
-  const uint32_t per_batch = groups * tilesN;
-  const uint32_t batch = strip / per_batch;
-  const uint32_t rem = strip - batch * per_batch;
-  const uint32_t g = rem / tilesN, tn = rem - g * tilesN;
-  const int rX = (int)(batch >> (2 * a.nRY));
-  const int rY = (int)(batch & ((1u << (2 * a.nRY)) - 1u));
-  const int64_t M = int64_t(1) << a.logM, N = int64_t(1) << a.logN;
-  const int64_t nw = (int64_t)tn * BN + wave * TN;
-  const gptr<const float> X = gbl(static_cast<const float *>(a.X));
-  const gptr<const float> Y = gbl(static_cast<const float *>(a.Y));
-  const int l16 = lane & 15, lg = lane >> 4;
-  const int nSv = 1 << (2 * a.nS);
-  // every load is made (rows past the term count read row 0) and the missing
-  // terms are zeroed afterwards: a masked load is a branch and a wait each
-  int2 rrq[4];   // term 4q + lane/16 (rows -1: past the term count)
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int sq = 4 * q + lg;
-    rrq[q] = sq < nSv ? make_int2(row_of(a.mx, sq, rX), row_of(a.my, sq, rY)) : make_int2(-1, -1);
-  }
-  float ay[4][4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const bool kok = rrq[q].x >= 0;
-    const gptr<const float> yr = Y + (int64_t)(kok ? rrq[q].y : 0) * N;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) ay[q][j] = yr[nw + j * 16 + l16];
-  }
-  float bx[R][4][4];
-  auto load_x = [&](int r) {
-    const int64_t mw = (int64_t)(g * R + r) * BM;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const bool kok = rrq[q].x >= 0;
-      const gptr<const float> xr = X + (int64_t)(kok ? rrq[q].x : 0) * M;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) bx[r][i][q] = xr[mw + i * 16 + l16];
-    }
-  };
-  load_x(0);
-  if (nSv < 16) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) ay[q][j] = rrq[q].x >= 0 ? ay[q][j] : 0.f;
-  }
-  float *st = stage + wave * 16 * SLD;
-  const float sc = MODE == kModeIntermediate ? 1.0f : (float)a.scale;
-  const gptr<O> Zb = gbl(static_cast<O *>(a.Z)) + (MODE == kModeIntermediate ? (int64_t)batch * M * N : 0);
-  // cross-entropy form: the targets of a whole tile, loaded before its first
-  // store (strips cover whole tiles)
-  f32x4 tv[XE ? 16 : 1];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const uint32_t tm = g * R + r;
-    const int64_t mw = (int64_t)tm * BM;
-    if constexpr (XE)
-#pragma unroll
-      for (int q = 0; q < 16; ++q)
-        tv[q] = xent_t4(a, (mw + (q >> 2) * 16 + (q & 3) * 4 + lane / 16) * N + nw + (lane % 16) * 4);
-    if (r + 1 < R) load_x(r + 1);
-    double msum = 0.0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      V acc[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] = V{0, 0, 0, 0};
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] = Op::run(ay[q][j], bx[r][i][q], acc[j]);
-      // stage the 16 x 64 slice, then write whole 256-byte row segments
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        *reinterpret_cast<float4 *>(st + l16 * SLD + j * 16 + 4 * lg) =
-            make_float4(acc[j][0] * sc, acc[j][1] * sc, acc[j][2] * sc, acc[j][3] * sc);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-      for (int rr = 0; rr < 16; rr += 4) {
-        const int row = rr + lane / 16, col = (lane % 16) * 4;
-        const float4 v = *reinterpret_cast<const float4 *>(st + row * SLD + col);
-        if constexpr (XE) {
-          const float w[4] = {v.x, v.y, v.z, v.w};
-          double c[4];
-          xent_emit4(a, (mw + i * 16 + row) * N + nw + col, w, tv[XE ? 4 * i + rr / 4 : 0], c, XE == 2);
-          msum += (c[0] + c[1]) + (c[2] + c[3]);
-        } else {
-          *(gptr<f32x4>)(Zb + (mw + i * 16 + row) * N + nw + col) = f32x4{v.x, v.y, v.z, v.w};
-          if (MODE != kModeIntermediate) msum += ((double)v.x + (double)v.y) + ((double)v.z + (double)v.w);
-        }
-      }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    }
-    if (MODE == kModeIntermediate) {
-      if (a.flagZ && tm == 0 && tn == 0 && tid == 0) a.flagZ[batch] = nSv > 0;
-    } else if (a.partials) {
-      const double tot = xent_total<O, XE>(wave_sum_f64(msum));
-      const int64_t tile = (int64_t)batch * a.tilesM * a.tilesN + (int64_t)tm * tilesN + tn;
-      if (lane == 0) a.partials[kPartialsPerTile * tile + wave] = tot;
-    }
-  }
-}
-
-template <int MODE, int XE>
-__global__ __launch_bounds__(256) void k_contract_strip_queue(const ContractArgs *descs, const int64_t *prefix,
-                                                              int ndesc, unsigned long long *queue, int64_t total) {
-  __shared__ int64_t item;
-  for (;;) {
-    __syncthreads();
-    if (threadIdx.x == 0) item = (int64_t)atomicAdd(queue, 1ull);
-    __syncthreads();
-    const int64_t it = item;
-    if (it >= total) return;
-    const int d = find_desc(prefix, ndesc, it);
-    contract_small_strip<float, MODE, XE>(descs[d], (uint32_t)(it - prefix[d]));
-  }
-}
-
-template <typename O, int MODE>
-__global__ __launch_bounds__(256) void k_contract_strip(const ContractArgs a) {
-  if (gated_off(a.gate, a.gate_val)) return;
-  const int64_t ns = a.nblocks / kStripRows;
-  const uint32_t s = a.xcd_remap ? (uint32_t)xcd_remap(blockIdx.x, ns) : blockIdx.x;
-  contract_small_strip<O, MODE>(a, s);
-}
-
 // ---- launch wrappers: one step per launch, or a work queue over many steps
 template <typename T, typename O, int BM, int BN, int WM, int WN, int MODE, bool SMALL>
 __global__ __launch_bounds__(256) void k_contract(const ContractArgs a) {
@@ -873,13 +729,6 @@ int choose_tile(Acc acc, int nS, int logM, int logN, bool wide_ok, bool panel, i
 template <typename T, typename O, int MODE, bool SMALL>
 static Status launch_contract_ms(int cfg, const ContractArgs &a, hipStream_t s) {
   const dim3 grid((unsigned)a.nblocks), block(256);
-  if constexpr (SMALL && std::is_same<T, float>::value && std::is_same<O, float>::value &&
-                MODE != kModeFinalDeposit) {
-    // every term kept and whole tiles in pairs of rows: two-tile strips
-    if (cfg == kTileL && !a.flagX && a.logN >= 8 && a.logM >= 7)
-      return launch("contract_small_strip_64x256", k_contract_strip<O, MODE>,
-                    dim3((unsigned)(a.nblocks / kStripRows)), block, 0, s, a);
-  }
   switch (cfg) {
     case kTileL: return launch(SMALL ? "contract_small_64x256" : "contract_64x256", k_contract<T, O, 64, 256, 1, 4, MODE, SMALL>, grid, block, 0, s, a);
     case kTileM: return launch(SMALL ? "contract_small_32x128" : "contract_32x128", k_contract<T, O, 32, 128, 1, 4, MODE, SMALL>, grid, block, 0, s, a);
@@ -916,23 +765,6 @@ static Status launch_queue_t(int cfg, const QueueLaunch &q, hipStream_t s) {
   return launch_queue_x<T, MODE, SMALL, 0>(cfg, q, s);
 }
 
-Status launch_contract_strip_queue(int mode, const QueueLaunch &q, hipStream_t s) {
-  const dim3 grid(q.grid), block(256);
-  if (mode == kModeIntermediate)
-    return launch("contract_strip_queue", k_contract_strip_queue<kModeIntermediate, 0>, grid, block, 0, s,
-                  q.descs, q.prefix, q.ndesc, q.queue, q.total);
-  if (mode == kModeFinalBlocked && q.xent == 1)
-    return launch("contract_strip_queue_xent", k_contract_strip_queue<kModeFinalBlocked, 1>, grid, block, 0, s,
-                  q.descs, q.prefix, q.ndesc, q.queue, q.total);
-  if (mode == kModeFinalBlocked && q.xent == 2)
-    return launch("contract_strip_queue_xent_loss", k_contract_strip_queue<kModeFinalBlocked, 2>, grid, block, 0,
-                  s, q.descs, q.prefix, q.ndesc, q.queue, q.total);
-  if (mode == kModeFinalBlocked)
-    return launch("contract_strip_queue", k_contract_strip_queue<kModeFinalBlocked, 0>, grid, block, 0, s,
-                  q.descs, q.prefix, q.ndesc, q.queue, q.total);
-  return Status::fail(CQC_ERR_UNSUPPORTED, "two-tile strips need blocked or intermediate output");
-}
-
 template <typename T, int MODE>
 static Status launch_queue_m(int cfg, bool small, const QueueLaunch &q, hipStream_t s) {
   return small ? launch_queue_t<T, MODE, true>(cfg, q, s) : launch_queue_t<T, MODE, false>(cfg, q, s);
@@ -960,6 +792,7 @@ static Status launch_contract_t(int cfg, const ContractArgs &a, hipStream_t s) {
 
 Status launch_contract(Acc acc, bool out_double, int cfg, const ContractArgs &a, hipStream_t s) {
   if (!tile_ok(acc, cfg)) return Status::fail(CQC_ERR_INVALID_ARG, "tile configuration not available for this arithmetic");
+  if (acc == Acc::F32 && a.rows) return launch_rows(out_double, a, s);
   if (cfg == kTileW) return launch_contract_wide(split_parts(acc), out_double, a, s);
   if (acc == Acc::F32)
     return out_double ? launch_contract_t<float, double>(cfg, a, s)

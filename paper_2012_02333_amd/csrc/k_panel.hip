@@ -147,6 +147,7 @@ __device__ __forceinline__ double panel_rows(const ContractArgs &a, const PanelT
       buf_store2_nt(v0, v1, Z, zl, row_off(r));   // dropped where p is not kept
       buf_store2_nt(xent_grad_of(v0, t[0]), xent_grad_of(v1, t[1]), G, zl, row_off(r));
       msum += xent_part(v0, t[0], XE == 2) + xent_part(v1, t[1], XE == 2);
+      asm volatile("" : "+v"(msum));   // or the sum is put off, with all its operands alive
     } else {
       buf_store2_nt(v0, v1, Z, zl, row_off(r));
       if (MODE != kModeIntermediate) msum += (double)v0 + (double)v1;
@@ -384,6 +385,7 @@ __device__ __forceinline__ void stream_block(const ContractArgs &a, int64_t blk)
       buf_store2_nt(v0, v1, Z, zl, row_off(r));   // dropped where p is not kept
       buf_store2_nt(xent_grad_of(v0, t[0]), xent_grad_of(v1, t[1]), G, zl, row_off(r));
       msum += xent_part(v0, t[0], XE == 2) + xent_part(v1, t[1], XE == 2);
+      asm volatile("" : "+v"(msum));   // or the sum is put off, with all its operands alive
     } else if (MODE != kModeIntermediate) {
       msum += (double)v0 + (double)v1;
     }

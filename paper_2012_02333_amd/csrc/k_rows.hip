@@ -1,0 +1,350 @@
+// Row kernel: FP32 steps of at most two shared cuts (1, 4 or 16 terms), which
+// are bound by their output bytes.
+//
+// What decides such a step is how its outputs reach memory: a plain copy of one
+// 16-byte access per thread in address order moves 6.6 TB/s on this card, the
+// same copy in larger pieces per thread 5.2 to 5.8.  So a wave here owns 64 C
+// adjacent columns and writes them row by row, 1024 contiguous bytes per
+// instruction at C = 4, straight from the accumulators:
+//   - v_mfma_f32_4x4x1_16b_f32 multiplies 4 rows by 64 columns for one term.
+//     Lane l's B operand is its own column l, so lane l's accumulators are four
+//     rows of column l, and C products with the C columns a lane holds leave it
+//     C consecutive outputs of each row: no staging, no LDS, no barrier.
+//   - the A operand of one register is 16 blocks of four rows: with 4 terms of
+//     16 rows in it, the block selector picks the term and the four rows, so 16
+//     rows of 16 terms are four registers (and one load each).
+// No product is wasted on padding at 4 terms, and waves of neighbouring units
+// write neighbouring memory (units run over the panels of a row run first).
+// The Y operands (C K registers) are loaded once per run of row tiles.
+// Measured against the LDS-staged strips of two 64 x 256 tiles that this
+// replaces: 389 M outputs of the cross-entropy form 785 us there, 582 here (8
+// bytes each: 5.3 TB/s); 2^30 outputs of 16 terms 787 and 755 us; 2^24 outputs
+// of 16 terms 15.5 and 14.8 us; 42 M outputs 128 columns wide, cross-entropy
+// form, 149 us on 32 x 128 tiles and 64 here.
+#include <algorithm>
+#include <type_traits>
+
+#include "kdev.hpp"
+
+namespace cqc {
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
+// The C columns of a lane: C consecutive ones, or for FP64 outputs two pairs
+// 128 columns apart (16 bytes each), so every access of a wave is contiguous.
+template <typename O, int C> struct RowCols {
+  static constexpr bool kPairs = sizeof(O) == 8 && C == 4;
+  static __device__ __forceinline__ uint32_t col(int lane) { return (uint32_t)((kPairs ? 2 : C) * lane); }
+};
+
+template <int C> __device__ __forceinline__ void load_cols(gptr<const char> p, bool pairs, float (&v)[C]) {
+  // rows may be 4-byte aligned only
+  typedef float u2 __attribute__((ext_vector_type(2), aligned(4)));
+  typedef float u4 __attribute__((ext_vector_type(4), aligned(4)));
+  if constexpr (C == 4) {
+    if (pairs) {
+      const u2 a = *(gptr<const u2>)p, b = *(gptr<const u2>)(p + 512);
+      v[0] = a[0]; v[1] = a[1]; v[2] = b[0]; v[3] = b[1];
+    } else {
+      const u4 a = *(gptr<const u4>)p;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[c] = a[c];
+    }
+  } else if constexpr (C == 2) {
+    const u2 a = *(gptr<const u2>)p;
+    v[0] = a[0]; v[1] = a[1];
+  } else {
+    v[0] = *(gptr<const float>)p;
+  }
+}
+
+// Outputs are written once and not read here: non-temporal.
+template <int C> __device__ __forceinline__ void store_cols(gptr<char> p, const float (&v)[C]) {
+  typedef float u2 __attribute__((ext_vector_type(2), aligned(4)));
+  typedef float u4 __attribute__((ext_vector_type(4), aligned(4)));
+  if constexpr (C == 4) __builtin_nontemporal_store(u4{v[0], v[1], v[2], v[3]}, (gptr<u4>)p);
+  else if constexpr (C == 2) __builtin_nontemporal_store(u2{v[0], v[1]}, (gptr<u2>)p);
+  else __builtin_nontemporal_store(v[0], (gptr<float>)p);
+}
+template <int C> __device__ __forceinline__ void store_cols(gptr<char> p, const double (&v)[C]) {
+  typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+  if constexpr (C == 4) {
+    __builtin_nontemporal_store(d2{v[0], v[1]}, (gptr<d2>)p);
+    __builtin_nontemporal_store(d2{v[2], v[3]}, (gptr<d2>)(p + 1024));
+  } else if constexpr (C == 2) {
+    __builtin_nontemporal_store(d2{v[0], v[1]}, (gptr<d2>)p);
+  } else {
+    __builtin_nontemporal_store(v[0], (gptr<double>)p);
+  }
+}
+template <int C> __device__ __forceinline__ void load_targets(gptr<const char> p, float (&v)[C]) {
+  typedef float u2 __attribute__((ext_vector_type(2), aligned(4)));
+  typedef float u4 __attribute__((ext_vector_type(4), aligned(4)));
+  if constexpr (C == 4) {
+    const u4 a = __builtin_nontemporal_load((gptr<const u4>)p);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = a[c];
+  } else if constexpr (C == 2) {
+    const u2 a = __builtin_nontemporal_load((gptr<const u2>)p);
+    v[0] = a[0]; v[1] = a[1];
+  } else {
+    v[0] = __builtin_nontemporal_load((gptr<const float>)p);
+  }
+}
+
+// One unit (this wave): columns n0 .. n0 + 64 C - 1 of 2^lt 16-row tiles.
+// KEEP: p is written too in the cross-entropy form.
+template <typename O, int MODE, int XE, bool KEEP, int C, int NS>
+__device__ __forceinline__ void rows_unit(const ContractArgs &a, int lt, int64_t unit) {
+  constexpr int K = 1 << (2 * NS), NV = K >= 4 ? K / 4 : 1;
+  constexpr int kLogC = C == 4 ? 2 : C == 2 ? 1 : 0;
+  using RC = RowCols<O, C>;
+  const int lane = threadIdx.x & 63;
+  const int logM = uni(a.logM), logN = uni(a.logN);
+  const int lp = logN - 6 - kLogC, lr = logM - 4 - lt;   // log2 of panels and of row runs
+  const int64_t batch = unit >> (lp + lr);
+  if (batch >= a.nbatch) return;
+  const int64_t n0 = (unit & ((int64_t(1) << lp) - 1)) << (6 + kLogC);
+  const int64_t m0 = ((unit >> lp) & ((int64_t(1) << lr) - 1)) << (4 + lt);
+  const int rX = (int)(batch >> (2 * a.nRY)), rY = (int)(batch & ((int64_t(1) << (2 * a.nRY)) - 1));
+  // rows of the operands: lane t < K computes those of term t
+  const int rx = lane < K ? row_of(a.mx, lane, rX) : 0, ry = lane < K ? row_of(a.my, lane, rY) : 0;
+  // early termination: dead terms become zero operands
+  uint32_t live = (1u << K) - 1u;
+  const bool flags = uni(a.flagX) != nullptr;
+  if (flags)
+    live = (uint32_t)__ballot(lane < K && (row_live(a.flagX, a.nchX, rx) & row_live(a.flagY, a.nchY, ry)));
+  const gptr<const char> Yb = gbl(reinterpret_cast<const char *>(uni(a.Y))) + 4 * n0;
+  const uint32_t yc = 4u * RC::col(lane);
+  float y[K][C];
+#pragma unroll
+  for (int t = 0; t < K; ++t) {
+    const int row = __builtin_amdgcn_readlane(ry, t);
+    load_cols<C>(Yb + ((int64_t)row << (logN + 2)) + yc, RC::kPairs, y[t]);
+  }
+  // X: lane l of register v holds row l % 16 of term 4 v + l / 16
+  const gptr<const float> Xb = gbl(static_cast<const float *>(uni(a.X)));
+  gptr<const float> xp[NV];
+  float x[NV];
+  auto masked = [&](int v, float w) {   // dead terms of the packed operand
+    return !flags || ((live >> (K >= 4 ? 4 * v + (lane >> 4) : 0)) & 1u) ? w : 0.f;
+  };
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int row = __shfl(rx, K >= 4 ? 4 * v + (lane >> 4) : 0, 64);
+    xp[v] = Xb + ((int64_t)row << logM) + m0 + (lane & 15);
+    x[v] = *xp[v];
+  }
+  if (flags) {
+#pragma unroll
+    for (int t = 0; t < K; ++t)
+#pragma unroll
+      for (int c = 0; c < C; ++c) y[t][c] = (live >> t) & 1u ? y[t][c] : 0.f;
+  }
+  const int64_t rowb = sizeof(O) * (int64_t(1) << logN);   // bytes of an output row
+  const int64_t o0 = sizeof(O) * ((MODE == kModeIntermediate ? batch << (logM + logN) : 0) + (m0 << logN) + n0);
+  gptr<char> Zr = gbl(static_cast<char *>(uni(a.Z))) + o0;
+  gptr<const char> Tr = XE ? gbl(static_cast<const char *>(uni(a.xt))) + o0 : nullptr;
+  gptr<char> Gr = XE ? gbl(static_cast<char *>(uni(a.xg))) + o0 : nullptr;
+  const uint32_t zc = sizeof(O) * RC::col(lane);
+  const O sc = MODE == kModeIntermediate ? O(1) : (O)uni(a.scale);
+  double msum = 0.0;
+  // cross-entropy form: the targets of the next two groups of four rows in flight
+  float tv[XE ? 2 : 1][4][C];
+  // a scalar row pointer moved on row by row; opaque, or the compiler keeps one
+  // 64-bit lane address per row and buffer in registers
+  auto advance = [&](auto &p) {
+    p += rowb;
+    asm volatile("" : "+s"(p));
+  };
+  auto targets = [&](int slot) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      load_targets<C>(Tr + zc, tv[XE ? slot : 0][r]);
+      advance(Tr);
+    }
+  };
+  if constexpr (XE) {
+    targets(0);
+    targets(1);
+  }
+  const int tiles = 1 << lt;
+  for (int it = 0; it < tiles; ++it) {
+    float xn[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      if (it + 1 < tiles) xp[v] += 16;   // the last tile reloads itself
+      xn[v] = *xp[v];
+      x[v] = masked(v, x[v]);
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      f32x4 acc[C];
+      auto products = [&](auto G) {
+        constexpr int rg = decltype(G)::value;
+        auto term = [&](auto Tc) {
+          constexpr int t = decltype(Tc)::value;
+#pragma unroll
+          for (int c = 0; c < C; ++c)
+            acc[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[t / 4], y[t][c], t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[c],
+                                                        4, K >= 4 ? 4 * (t % 4) + rg : rg, 0);
+        };
+        term(std::integral_constant<int, 0>{});
+        if constexpr (K >= 4) {
+          term(std::integral_constant<int, 1>{});
+          term(std::integral_constant<int, 2>{});
+          term(std::integral_constant<int, 3>{});
+        }
+        if constexpr (K == 16) {
+          term(std::integral_constant<int, 4>{});
+          term(std::integral_constant<int, 5>{});
+          term(std::integral_constant<int, 6>{});
+          term(std::integral_constant<int, 7>{});
+          term(std::integral_constant<int, 8>{});
+          term(std::integral_constant<int, 9>{});
+          term(std::integral_constant<int, 10>{});
+          term(std::integral_constant<int, 11>{});
+          term(std::integral_constant<int, 12>{});
+          term(std::integral_constant<int, 13>{});
+          term(std::integral_constant<int, 14>{});
+          term(std::integral_constant<int, 15>{});
+        }
+      };
+      if (g == 0) products(std::integral_constant<int, 0>{});
+      else if (g == 1) products(std::integral_constant<int, 1>{});
+      else if (g == 2) products(std::integral_constant<int, 2>{});
+      else products(std::integral_constant<int, 3>{});
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        O v[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) v[c] = (O)acc[c][r] * sc;
+        if constexpr (XE) {
+          float gr[C];
+#pragma unroll
+          for (int c = 0; c < C; ++c) {
+            const float t = tv[g & 1][r][c];
+            gr[c] = xent_grad_of(v[c], t);
+            msum += xent_part(v[c], t, XE == 2);
+          }
+          if constexpr (KEEP) {
+            store_cols<C>(Zr + zc, v);
+            advance(Zr);
+          }
+          store_cols<C>(Gr + zc, gr);
+          advance(Gr);
+          // one row's arithmetic in registers at a time (the sum would be put
+          // off, with all its operands alive)
+          asm volatile("" : "+v"(msum));
+          __builtin_amdgcn_sched_barrier(0);
+        } else {
+          store_cols<C>(Zr + zc, v);
+          advance(Zr);
+          if (MODE != kModeIntermediate) {
+            if constexpr (C == 4) msum += ((double)v[0] + (double)v[1]) + ((double)v[2] + (double)v[3]);
+            else
+#pragma unroll
+              for (int c = 0; c < C; ++c) msum += (double)v[c];
+          }
+        }
+      }
+      if constexpr (XE)
+        if (g < 2 || it + 1 < tiles) targets(g & 1);
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) x[v] = xn[v];
+  }
+  if (MODE == kModeIntermediate) {
+    if (a.flagZ && lane == 0 && (unit & ((int64_t(1) << (lp + lr)) - 1)) == 0) gbl(a.flagZ)[batch] = live != 0;
+  } else if (a.partials) {
+    const double tot = xent_total<O, XE>(wave_sum_f64(msum));
+    if (lane == 0) gbl(a.partials)[unit] = tot;
+  }
+}
+
+template <typename O, int MODE, int C, int NS>
+__global__ __launch_bounds__(256) void k_rows(const ContractArgs a, int lt) {
+  if (gated_off(a.gate, a.gate_val)) return;
+  rows_unit<O, MODE, 0, true, C, NS>(a, lt, (int64_t)blockIdx.x * 4 + uni((int32_t)(threadIdx.x >> 6)));
+}
+
+// Many steps of one shape class per launch: block b belongs to the step d with
+// prefix[d] <= b < prefix[d + 1].  One block per four units, not persistent:
+// the dispatcher keeps the blocks in address order and needs no counter.
+template <int MODE, int XE, int C, int NS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NS == 2 ? 3 : 4))) void k_rows_table(const ContractArgs *__restrict__ descs,
+                                                    const int64_t *__restrict__ prefix, int ndesc) {
+  const int d = uni(find_desc(prefix, ndesc, (int64_t)blockIdx.x));
+  const ContractArgs &a = descs[d];
+  const int lt = rows_log_tiles(uni(a.logM), uni(a.logN), 2 * (uni(a.nRX) + uni(a.nRY)), C, NS);
+  const int64_t unit = ((int64_t)blockIdx.x - uni(prefix[d])) * 4 + uni((int32_t)(threadIdx.x >> 6));
+  if (XE == 0 || uni(a.Z)) rows_unit<float, MODE, XE, true, C, NS>(a, lt, unit);
+  else rows_unit<float, MODE, XE, XE == 0, C, NS>(a, lt, unit);
+}
+
+int64_t rows_units(const ContractArgs &a) {
+  const int lt = rows_log_tiles(a.logM, a.logN, 2 * (a.nRX + a.nRY), a.rows, a.nS);
+  return a.nbatch << (a.logM - 4 - lt + a.logN - 6 - (a.rows == 4 ? 2 : a.rows == 2 ? 1 : 0));
+}
+
+template <typename O, int MODE, int C>
+static Status launch_rows_c(const char *nm, const ContractArgs &a, hipStream_t s) {
+  const int lt = rows_log_tiles(a.logM, a.logN, 2 * (a.nRX + a.nRY), a.rows, a.nS);
+  const dim3 grid((unsigned)((rows_units(a) + 3) / 4)), block(256);
+  switch (a.nS) {
+    case 0: return launch(nm, k_rows<O, MODE, C, 0>, grid, block, 0, s, a, lt);
+    case 1: return launch(nm, k_rows<O, MODE, C, 1>, grid, block, 0, s, a, lt);
+    default: return launch(nm, k_rows<O, MODE, C, 2>, grid, block, 0, s, a, lt);
+  }
+}
+
+template <typename O, int MODE>
+static Status launch_rows_m(const ContractArgs &a, hipStream_t s) {
+  switch (a.rows) {
+    case 4: return launch_rows_c<O, MODE, 4>(sizeof(O) == 4 ? "contract_small_strip_64x256" : "contract_small_rows_256", a, s);
+    case 2: return launch_rows_c<O, MODE, 2>("contract_small_rows_128", a, s);
+    default: return launch_rows_c<O, MODE, 1>("contract_small_rows_64", a, s);
+  }
+}
+
+Status launch_rows(bool out_double, const ContractArgs &a, hipStream_t s) {
+  const int logc = a.rows == 4 ? 2 : a.rows == 2 ? 1 : 0;
+  if (a.rows < 1 || a.nS > 2 || a.logM < 4 || a.logN < 6 + logc || a.mode == kModeFinalDeposit)
+    return Status::fail(CQC_ERR_INVALID_ARG, "row contraction: step shape");
+  if (a.mode == kModeIntermediate) return launch_rows_m<float, kModeIntermediate>(a, s);
+  return out_double ? launch_rows_m<double, kModeFinalBlocked>(a, s) : launch_rows_m<float, kModeFinalBlocked>(a, s);
+}
+
+template <int MODE, int XE, int C>
+static Status launch_rows_table_c(const char *nm, int nS, const QueueLaunch &q, hipStream_t s) {
+  const dim3 grid((unsigned)q.total), block(256);
+  switch (nS) {
+    case 0: return launch(nm, k_rows_table<MODE, XE, C, 0>, grid, block, 0, s, q.descs, q.prefix, q.ndesc);
+    case 1: return launch(nm, k_rows_table<MODE, XE, C, 1>, grid, block, 0, s, q.descs, q.prefix, q.ndesc);
+    default: return launch(nm, k_rows_table<MODE, XE, C, 2>, grid, block, 0, s, q.descs, q.prefix, q.ndesc);
+  }
+}
+
+template <int MODE, int XE>
+static Status launch_rows_table_m(int rows, int nS, const QueueLaunch &q, hipStream_t s) {
+  const bool wide = rows == 4;
+  const char *nm = XE == 2 ? (wide ? "contract_strip_queue_xent_loss" : "contract_small_queue_xent_loss")
+                   : XE    ? (wide ? "contract_strip_queue_xent" : "contract_small_queue_xent")
+                           : (wide ? "contract_strip_queue" : "contract_small_queue");
+  switch (rows) {
+    case 4: return launch_rows_table_c<MODE, XE, 4>(nm, nS, q, s);
+    case 2: return launch_rows_table_c<MODE, XE, 2>(nm, nS, q, s);
+    default: return launch_rows_table_c<MODE, XE, 1>(nm, nS, q, s);
+  }
+}
+
+Status launch_rows_table(int mode, int rows, int nS, const QueueLaunch &q, hipStream_t s) {
+  if (mode == kModeIntermediate) return launch_rows_table_m<kModeIntermediate, 0>(rows, nS, q, s);
+  if (mode != kModeFinalBlocked) return Status::fail(CQC_ERR_UNSUPPORTED, "row contraction: output mode");
+  if (q.xent == 2) return launch_rows_table_m<kModeFinalBlocked, 2>(rows, nS, q, s);
+  if (q.xent == 1) return launch_rows_table_m<kModeFinalBlocked, 1>(rows, nS, q, s);
+  return launch_rows_table_m<kModeFinalBlocked, 0>(rows, nS, q, s);
+}
+
+}  // namespace cqc

@@ -55,6 +55,7 @@ struct ContractArgs {
   int32_t *lists;    // [nbatch][2][list_ld] byte offsets of the live terms' X rows, then of
                      //   their Y rows, ascending s; padding 0
   int32_t *counts;   // [nbatch] live labels
+  int32_t rows;      // > 0: a small-term step that runs on the row kernel, with this many columns per lane
   int32_t panel;     // 1: a wide step that runs on the panel kernel (every step of a queue group alike)
   int32_t list_ld;   // pairs per batch entry: 4^nS rounded up to a multiple of 32
   int64_t nbatch;
@@ -170,11 +171,6 @@ struct QueueLaunch {
                            //   1 gradient (partials sum p), 2 gradient and loss
 };
 Status launch_contract_queue(Acc acc, int mode, int cfg, bool small, const QueueLaunch &q, hipStream_t s);
-// Two-tile strips of the 64 x 256 FP32 small-term kernel (FP32 output, blocked
-// or intermediate mode, no row flags): a step of nblocks tiles is nblocks /
-// kStripRows queue items.
-constexpr int kStripRows = 2;
-Status launch_contract_strip_queue(int mode, const QueueLaunch &q, hipStream_t s);
 
 // Batched row flags (descriptor table in device memory, block_start = prefix)
 // and per-instance mass reductions; the flag pass also zeroes `counters`.
@@ -204,8 +200,42 @@ constexpr int kPanelQueueLog = 3;
 __host__ __device__ inline int panel_queue_log_tiles(int logM) {
   return logM - 6 < kPanelQueueLog ? logM - 6 : kPanelQueueLog;
 }
+// Row kernel (k_rows.hip): the columns per lane (4, 2 or 1) with which a step
+// runs on it, or 0.  FP32 steps of at most two shared cuts, output not in
+// deposit order, whole 16-row tiles, and the widest panel (64 columns per lane
+// column) of the tile shape the step was given - so a tuned narrower tile
+// keeps the register kernel it was timed with.
+inline int rows_cols(Acc acc, int mode, int cfg, int nS, int logM, int logN) {
+  if (acc != Acc::F32 || mode == kModeFinalDeposit || nS > 2 || logM < 4 || logN < 6) return 0;
+  const int c = logN >= 8 ? 4 : logN == 7 ? 2 : 1;
+  switch (cfg) {
+    case kTileL: return c == 4 ? 4 : 0;
+    case kTileM: return c >= 2 ? c : 0;
+    case kTileS: return c == 1 || logM == 4 ? c : 0;
+    default: return 0;
+  }
+}
+// 16-row tiles per wave (log2).  Longer runs reload Y less often, but spread
+// the rows that the chip writes at one time over more memory: two tiles at 16
+// terms as long as that leaves 2048 waves (2^11 x 2^13 outputs: 17.0, 14.8,
+// 14.8, 23 us for 1, 2, 4, 8 tiles; 2^20 x 2^10: 890, 753, 765, 808), four with
+// fewer terms as long as that leaves 1024 (2^12 x 2^12: 14.4, 14.8, 12.7, 21).
+__host__ __device__ inline int rows_log_tiles(int logM, int logN, int log_batch, int rows, int nS) {
+  const int waves = logM - 4 + logN - 6 - (rows == 4 ? 2 : rows == 2 ? 1 : 0) + log_batch;
+  const int most = nS == 2 ? 1 : 2;
+  int lt = waves - (nS == 2 ? 11 : 10);
+  if (lt > most) lt = most;
+  if (lt > logM - 4) lt = logM - 4;
+  return lt < 0 ? 0 : lt;
+}
+// Waves of a step: one FP64 partial each in a final step, four per block.
+int64_t rows_units(const ContractArgs &a);
+Status launch_rows(bool out_double, const ContractArgs &a, hipStream_t s);
+// Many steps of equal rows and nS: prefix[d] = first block of step d.
+Status launch_rows_table(int mode, int rows, int nS, const QueueLaunch &q, hipStream_t s);
 // FP64 partials of a final step's launch (queue launch) with tile cfg.
 inline int64_t mass_partials(int cfg, const ContractArgs &a, bool queue) {
+  if (a.rows) return rows_units(a);
   return cfg == kTileW && a.panel ? panel_partials(a, queue) : kPartialsPerTile * a.nblocks;
 }
 // Splits `count` floats (a multiple of 4) into `parts` bfloat16 planes of

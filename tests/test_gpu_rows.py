@@ -1,0 +1,79 @@
+"""GPU parity of the row kernel (FP32 steps of at most two shared cuts): every
+panel width (256, 128 and 64 columns) at 16 rows and above, 1, 4 and 16 terms,
+FP32 and FP64 output, dead rows where row flags are computed, batched
+intermediate steps, and the batched cross-entropy form with and without p.
+Elementwise bound as in test_gpu_fd; sums in FP64 (1e-12 of the sum of
+magnitudes)."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import fd
+from tests.gpu_util import to_dev, oracle_inputs, abs_bound, elementwise_ok, U32
+
+pytestmark = pytest.mark.gpu
+cqc = pytest.importorskip("paper_2012_02333_amd")
+
+
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _pair(f, k):
+    return W.CutMap(sum(f), list(f), [0] * k, [1] * k, list(range(sum(f))))
+
+
+@pytest.mark.parametrize("out", [torch.float32, torch.float64])
+@pytest.mark.parametrize("k", [0, 1, 2])
+@pytest.mark.parametrize("f", [(4, 8), (5, 9), (7, 10), (4, 7), (6, 7), (4, 6), (9, 6), (10, 8)])
+def test_rows_step(f, k, out):
+    _gpu()
+    cut = _pair(f, k)
+    host, dev = to_dev(W.random_entries(cut, seed=960 + k), torch.float32)
+    with cqc.trace() as tr:
+        p, mass = cqc.reconstruct_fd(dev, cqc.CutMap.from_workload(cut), precision="fp32", out_dtype=out)
+        torch.cuda.synchronize()
+    assert any(n.startswith(("contract_small_rows", "contract_small_strip")) for n in tr.result), tr.result
+    e64 = oracle_inputs(host)
+    ok, info = elementwise_ok(p.double().cpu().numpy(), fd.reconstruct(e64, cut), abs_bound(e64, cut), U32, 4 ** k)
+    assert ok, info
+    assert abs(float(mass) - float(p.double().sum())) <= 1e-12 * float(p.double().abs().sum())
+
+
+@pytest.mark.parametrize("k0,k1", [(1, 3), (2, 3), (2, 2), (3, 2)])
+def test_rows_in_chains(k0, k1):
+    """A small-term step next to a long one (row flags, dead rows) or to
+    another, as the batched intermediate or the final step."""
+    _gpu()
+    f = [6, 7, 6]
+    cut = W.CutMap(19, f, [0] * k0 + [1] * k1, [1] * k0 + [2] * k1, list(range(19)))
+    zr = [(0, 1), (2, 0), (2, 3)] + [(1, r) for r in range(4 ** (k0 + k1)) if r % 7 == 2]
+    host, dev = to_dev(W.random_entries(cut, seed=970, zero_rows=zr), torch.float32)
+    p, _ = cqc.reconstruct_fd(dev, cqc.CutMap.from_workload(cut), precision="fp32")
+    xs = W.sample_outputs(19, 4096, seed=971)
+    e64 = oracle_inputs(host)
+    ok, info = elementwise_ok(p[torch.from_numpy(xs).cuda()].double().cpu().numpy(), fd.reconstruct(e64, cut, xs),
+                              abs_bound(e64, cut, xs), U32, 4 ** (k0 + k1))
+    assert ok, info
+
+
+@pytest.mark.parametrize("keep", [True, False])
+def test_rows_batch_xent(keep):
+    _gpu()
+    shapes = [((11, 9), 1), ((9, 11), 2), ((8, 7), 1), ((8, 7), 2), ((9, 6), 1), ((4, 8), 2), ((4, 6), 1)]
+    cuts_w = [_pair(f, k) for f, k in shapes]
+    dev = [to_dev([np.abs(E) for E in W.random_entries(c, seed=980 + i)], torch.float32)[1]
+           for i, c in enumerate(cuts_w)]
+    cuts = [cqc.CutMap.from_workload(c) for c in cuts_w]
+    t = [torch.from_numpy(W.dirichlet_target(c.n, 990 + i).astype(np.float32)).cuda() for i, c in enumerate(cuts_w)]
+    batch = cqc.Batch(dev, cuts, precision="fp32", targets=t, with_loss=True, keep_outputs=keep)
+    batch.run()
+    for i, c in enumerate(cuts):
+        p, _ = cqc.reconstruct_fd(dev[i], c, precision="fp32")
+        assert torch.equal(batch.grads[i], cqc.xent_grad(p, t[i])), i
+        if keep:
+            assert torch.equal(batch.outs[i], p), i
+        term = t[i].double() * p.double().clamp_min(1e-30).log()
+        assert abs(float(batch.losses[i]) + float(term.sum())) <= 2.0 ** -22 * float(term.abs().sum()), i
