@@ -45,6 +45,8 @@ struct TopOut {
 constexpr int kMergeLogChunk = 12;
 // Chunks per output of a merge over 2^n_merged combinations (log2).
 inline int merge_log_chunks(int n_merged) { return n_merged > kMergeLogChunk ? n_merged - kMergeLogChunk : 0; }
+// Lanes that add the chunk sums of one output (log2).
+__host__ __device__ inline int merge_chunk_lanes(int log_chunks) { return log_chunks < 6 ? log_chunks : 6; }
 // Whether a short merge can take the segmented path (see k_dd_merge).
 inline bool merge_segmented(int n_merged, int active_shift, int merged_shift) {
   return n_merged >= 1 && n_merged < 6 && merged_shift == 0 && active_shift == n_merged;

@@ -38,6 +38,23 @@ __global__ __launch_bounds__(256) void k_dd_merge(const MergeArgs a) {
     const I *row = E + r * f;
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     const int64_t m1 = (ch + 1) * clen;
+    constexpr int kV = 16 / sizeof(I);   // elements per 16-byte load
+    if (msh == 0 && clen >= 64 * kV * 4) {
+      // the chunk is one run of memory (the merged bits are the lowest): four
+      // 16-byte loads in flight per lane.  Bound by the read of the entries
+      // (each element once): at 4 bytes per load 3.3 GB took 908 us, 3.6 TB/s.
+      typedef I vec __attribute__((ext_vector_type(kV), aligned(sizeof(I))));
+      const gptr<const I> run = gbl(row + base) + ch * clen;
+      for (int64_t m0 = kV * lane; m0 < clen; m0 += 64 * kV * 4) {
+        vec v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = __builtin_nontemporal_load((gptr<const vec>)(run + m0 + u * 64 * kV));
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int e = 0; e < kV; ++e) acc[(u * kV + e) % 8] += (double)v[u][e];
+      }
+    } else
     for (int64_t m0 = ch * clen + lane; m0 < m1; m0 += 8 * 64) {
       double v[8];
 #pragma unroll
@@ -91,8 +108,11 @@ __global__ __launch_bounds__(256) void k_dd_merge(const MergeArgs a) {
   }
 }
 
-// Second pass of long merges: one thread per output adds its chunk sums in
-// chunk order.  Descriptors without chunks have no blocks here.
+// Second pass of long merges: the chunk sums of an output by an aligned group
+// of lanes, one per chunk up to a wave (each lane adds its strided chunks in
+// order, then a butterfly: a fixed order).  With one thread per output the 528
+// sums of 256 chunks of a 100-qubit query took 39 us.  Descriptors without
+// chunks have no blocks here.
 template <typename O>
 __global__ __launch_bounds__(256) void k_dd_merge_chunks(const MergeArgs a) {
   if (gated_off(a.gate, a.gate_val)) return;
@@ -100,14 +120,19 @@ __global__ __launch_bounds__(256) void k_dd_merge_chunks(const MergeArgs a) {
   int i = 0;
   while (i + 1 < a.n && bid >= a.d[i + 1].chunk_block_start) ++i;
   const MergeDesc &d = a.d[i];
-  const int64_t o = (bid - d.chunk_block_start) * 256 + threadIdx.x;
+  const int ll = merge_chunk_lanes(d.log_chunks);
+  const int64_t g = (bid - d.chunk_block_start) * 256 + threadIdx.x;
+  const int64_t o = g >> ll;
   const int64_t nout = d.rows << d.n_active;
-  if (d.log_chunks == 0 || o >= nout) return;
+  if (d.log_chunks == 0 || o >= nout) return;   // whole groups leave together
   const int64_t nc = int64_t(1) << d.log_chunks;
-  const double *p = d.part + o * nc;
+  const gptr<const double> p = gbl(d.part + o * nc);
+  const int l = (int)(g & ((1 << ll) - 1));
   double s = 0.0;
-  for (int64_t c = 0; c < nc; ++c) s += p[c];
-  static_cast<O *>(d.dst)[o] = (O)s;
+#pragma unroll 4
+  for (int64_t c = l; c < nc; c += 1 << ll) s += p[c];
+  for (int k = (1 << ll) >> 1; k >= 1; k >>= 1) s += __shfl_xor(s, k, 64);
+  if (l == 0) static_cast<O *>(d.dst)[o] = (O)s;
 }
 
 // ---- top-T of FP64 bins, ordered by (value descending, index ascending)
@@ -307,7 +332,7 @@ Status launch_dd_merge(const MergeArgs &a, int64_t blocks, bool in_double, bool 
   int64_t nb = 0;
   for (int i = 0; i < c.n; ++i) {
     c.d[i].chunk_block_start = nb;
-    if (c.d[i].log_chunks > 0) nb += ((c.d[i].rows << c.d[i].n_active) + 255) / 256;
+    if (c.d[i].log_chunks > 0) nb += ((c.d[i].rows << (c.d[i].n_active + merge_chunk_lanes(c.d[i].log_chunks))) + 255) / 256;
   }
   if (nb == 0) return Status::ok();
   const dim3 g2((unsigned)nb);
