@@ -160,3 +160,24 @@ def test_eigen_form_end_to_end_and_smaller_kappa():
         assert metrics.rel_l1(p32.double().cpu().numpy(), truth) < 1e-6, form
         kap[form] = metrics.kappa([E.cpu().numpy() for E in Es], cut, np.abs(truth).sum())
     assert kap["eigen"] < kap["pauli"], kap
+
+
+@pytest.mark.parametrize("form", ["pauli", "eigen"])
+@pytest.mark.parametrize("kinds", [[0], [0, 0], [1], [1, 1]])
+@pytest.mark.parametrize("f", [1, 2, 3, 10, 11])
+def test_one_sided_cuts_fp32(kinds, f, form):
+    """One or two cuts of one kind in FP32 (several columns per thread): the
+    smallest column counts, a partly filled block, and variants and entries at
+    a 4-byte aligned address; one FP32 rounding of the FP64 result."""
+    _gpu()
+    k_in, k_out = kinds.count(0), kinds.count(1)
+    V = W.random_variants(k_in, k_out, f, seed=50 + f).astype(np.float32)
+    vb = torch.empty(V.size + 1, dtype=torch.float32, device="cuda")
+    vb[1:].copy_(torch.from_numpy(V.reshape(-1)))
+    eb = torch.full((4 ** len(kinds) * 2 ** f + 2,), 7.0, device="cuda")
+    E = eb[1:-1].view(4 ** len(kinds), 2 ** f)
+    cqc.build_entries([(vb[1:].view(V.shape), kinds)], outs=[E], form=form)
+    ref = variants.entries_from_variants(V.astype(np.float64), kinds, form=form)
+    got = E.double().cpu().numpy()
+    assert np.all(np.abs(got - ref) <= 2.0 ** -24 * np.abs(ref) + 1e-13)
+    assert float(eb[0]) == 7.0 and float(eb[-1]) == 7.0
