@@ -69,7 +69,7 @@ static int queue_cfg(Acc acc, const Plan &p, size_t si, int mode, bool out_doubl
   const Step &st = p.steps[si];
   const Acc sa = step_acc(acc, st.wide_ok(), (int)st.S.size());
   const int nS = (int)st.S.size();
-  int c = choose_tile(sa, nS, st.logM, st.logN, st.wide_ok(), panel_step(p, si), st.nbatch);
+  int c = choose_tile(sa, nS, st.logM, st.logN, st.wide_ok(), panel_step(p, si), st.nbatch, false);
   if (sa == Acc::F32 && st.wide_ok() && nS >= 3 && (panel_step(p, si) || (st.logM >= 7 && st.logN >= 7)) &&
       (int64_t(1) << (st.logM + st.logN)) * st.nbatch >= (int64_t(1) << kBatchWideLog))
     c = kTileW;
@@ -131,7 +131,7 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
         d.unit = ws + L.t_off[1];
         d.unit_flag = reinterpret_cast<int32_t *>(ws + L.f_off[1]);
       }
-      B.flag_blocks += T.rows() * flag_chunks(T.cols());
+      B.flag_blocks += flag_blocks(T.rows(), T.cols());
       B.flags.push_back(d);
     }
     for (size_t s = 0; s < p.steps.size(); ++s) {

@@ -38,7 +38,7 @@ NetLayout layout_net(const Plan &plan, Acc acc, size_t base) {
   for (size_t i = 0; i < plan.steps.size(); ++i) {
     const Step &st = plan.steps[i];
     int cfg = choose_tile(step_acc(acc, st.wide_ok(), (int)st.S.size()), (int)st.S.size(), st.logM, st.logN,
-                          st.wide_ok(), panel_step(plan, i), st.nbatch);
+                          st.wide_ok(), panel_step(plan, i), st.nbatch, spread_step(plan, i, acc));
     TileShape sh = tile_shape(cfg);
     int64_t tm = ((int64_t(1) << st.logM) + sh.bm - 1) / sh.bm;
     int64_t tn = ((int64_t(1) << st.logN) + sh.bn - 1) / sh.bn;
@@ -135,6 +135,8 @@ Status run_net(const NetLayout &L, char *ws, const std::vector<const void *> &en
     if (T.entry >= 0) tptr[t] = entries[T.entry];
     else tptr[t] = ws + L.t_off[t];
   }
+  // tensors that the step which made them left as bfloat16 parts (split plans)
+  std::vector<char> in_parts(nt, 0);
   const bool need_flags = needs_flags(L, skip_final);
   if (compute_entry_flags && need_flags) {
     FlagArgs fa;
@@ -150,7 +152,7 @@ Status run_net(const NetLayout &L, char *ws, const std::vector<const void *> &en
       d.cols = T.cols();
       d.flags = reinterpret_cast<int32_t *>(ws + L.f_off[t]);
       d.block_start = blocks;
-      blocks += T.rows() * flag_chunks(T.cols());
+      blocks += flag_blocks(T.rows(), T.cols());
     }
     fa.n = n;
     fa.is_double = L.acc == Acc::F64;
@@ -192,7 +194,7 @@ Status run_net(const NetLayout &L, char *ws, const std::vector<const void *> &en
     a.panel = sa == Acc::F32 && panel_step(p, i) && !od ? 1 : 0;
     // (the layout does not know the output dtype, which the panel kernel needs to be FP32)
     const int rule = od && sa == Acc::F32 && L.tile[i] == kTileW
-                         ? choose_tile(sa, a.nS, st.logM, st.logN, st.wide_ok(), false, st.nbatch) : L.tile[i];
+                         ? choose_tile(sa, a.nS, st.logM, st.logN, st.wide_ok(), false, st.nbatch, true) : L.tile[i];
     int cfg = rule, xcd = 0;
     // a cached choice is keyed by shape class, which does not fix the operand
     // heights: the wide tile also needs this step's operands to fit it
@@ -217,10 +219,27 @@ Status run_net(const NetLayout &L, char *ws, const std::vector<const void *> &en
       a.yplane = Y.rows() * Y.cols();
       a.Xs = ws + L.xs_off[i];
       a.Ys = ws + L.ys_off[i];
-      CQC_TRY(launch_presplit(split_parts(sa), static_cast<const float *>(a.X), ws + L.xs_off[i], a.xplane,
-                              a.xplane, s));
-      CQC_TRY(launch_presplit(split_parts(sa), static_cast<const float *>(a.Y), ws + L.ys_off[i], a.yplane,
-                              a.yplane, s));
+      if (!in_parts[st.x])
+        CQC_TRY(launch_presplit(split_parts(sa), static_cast<const float *>(a.X), ws + L.xs_off[i], a.xplane,
+                                a.xplane, s));
+      if (!in_parts[st.y])
+        CQC_TRY(launch_presplit(split_parts(sa), static_cast<const float *>(a.Y), ws + L.ys_off[i], a.yplane,
+                                a.yplane, s));
+    }
+    if (!last && a.Xs) {
+      // a result that only a split step of this run reads goes straight into
+      // that step's parts (writing it, reading it back and splitting it took
+      // two passes over it)
+      for (size_t j = i + 1; j < p.steps.size(); ++j) {
+        const Step &sj = p.steps[j];
+        if (sj.x != st.z && sj.y != st.z) continue;
+        if ((skip_final && j + 1 == p.steps.size()) || L.xs_off[j] == SIZE_MAX) break;
+        const TensorSpec &Z = p.tensors[st.z];
+        a.Zs = ws + (sj.x == st.z ? L.xs_off[j] : L.ys_off[j]);
+        a.zplane = Z.rows() * Z.cols();
+        in_parts[st.z] = 1;
+        break;
+      }
     }
     if (!last) {
       a.mode = kModeIntermediate;

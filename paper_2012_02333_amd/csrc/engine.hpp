@@ -63,4 +63,13 @@ inline bool panel_step(const Plan &p, size_t i) {
   return p.steps[i].panel_ok() && (i + 1 < p.steps.size() || is_blocked(p, p.steps[i]));
 }
 
+// Whether step i, launched by itself, should spread over small tiles
+// (choose_tile): not on the row kernel, which sizes its own units.
+inline bool spread_step(const Plan &p, size_t i, Acc acc) {
+  const Step &st = p.steps[i];
+  const bool rows = acc != Acc::F64 && st.S.size() <= 2 && st.logM >= 4 && st.logN >= 6 &&
+                    (i + 1 < p.steps.size() || is_blocked(p, st));
+  return !rows;
+}
+
 }  // namespace cqc

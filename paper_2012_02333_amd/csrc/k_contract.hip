@@ -568,49 +568,85 @@ __global__ __launch_bounds__(256) void k_contract_queue(const ContractArgs *desc
 }
 
 // ---------------------------------------------------------------------------
-// Row flags of the entry tensors: one block per (row, chunk of kFlagChunk
-// columns) writes whether that chunk has a non-zero element.  The first block
-// of a tensor that carries a unit operand (single-subcircuit plans) also
-// writes that operand's value 1 and its flag.
-__device__ __forceinline__ void flags_chunk(const FlagDesc &d, int64_t rc, bool is_double) {
+// Row flags of the entry tensors: whether a chunk of kFlagChunk columns of a row
+// has a non-zero element.  One wave per chunk, or per run of short rows that is
+// as long as a chunk, with all of it in flight (with a block per chunk and row
+// the 65536 rows of 512 columns of an eight-cut subcircuit took 67 us, FLAG_US
+// now).  The first wave of a tensor that carries a unit operand
+// (single-subcircuit plans) also writes that operand's value 1 and its flag.
+template <typename T>
+__device__ __forceinline__ void flags_wave(const FlagDesc &d, int64_t item) {
+  const int lane = threadIdx.x & 63;
   const int64_t nch = flag_chunks(d.cols);
-  const int64_t r = rc / nch, ch = rc - r * nch;
-  const int64_t c0 = ch * kFlagChunk;
-  const int64_t c1 = d.cols < c0 + kFlagChunk ? d.cols : c0 + kFlagChunk;
-  int any = 0;
-  if (is_double) {
-    const double *p = static_cast<const double *>(d.ptr) + r * d.cols;
-    if (d.cols % 2 == 0) {
-      const double2 *q = reinterpret_cast<const double2 *>(p);
-#pragma unroll 4
-      for (int64_t c = c0 / 2 + threadIdx.x; c < c1 / 2; c += blockDim.x) {
-        const double2 v = q[c];
-        any |= (v.x != 0.0) | (v.y != 0.0);
-      }
-    } else {
-      for (int64_t c = c0 + threadIdx.x; c < c1; c += blockDim.x) any |= (p[c] != 0.0);
+  const gptr<const T> base = gbl(static_cast<const T *>(d.ptr));
+  const gptr<int32_t> flags = gbl(d.flags);
+  constexpr int kV = 16 / sizeof(T), kL = kFlagChunk / (64 * kV);   // elements per load, loads per lane
+  typedef T vec __attribute__((ext_vector_type(kV), aligned(sizeof(T))));
+  if (d.cols < 4) {   // one or two columns: a row per lane
+    const int64_t r = item * flag_rows(d.cols) + lane;
+    if (r < d.rows) {
+      int any = 0;
+      for (int64_t c = 0; c < d.cols; ++c) any |= base[r * d.cols + c] != T(0);
+      flags[r] = any;
     }
-  } else {
-    const float *p = static_cast<const float *>(d.ptr) + r * d.cols;
-    if (d.cols % 4 == 0) {
-      const float4 *q = reinterpret_cast<const float4 *>(p);
-#pragma unroll 2
-      for (int64_t c = c0 / 4 + threadIdx.x; c < c1 / 4; c += blockDim.x) {
-        const float4 v = q[c];
-        any |= (v.x != 0.0f) | (v.y != 0.0f) | (v.z != 0.0f) | (v.w != 0.0f);
+    return;
+  }
+  if (nch > 1 || d.cols == kFlagChunk) {   // a chunk of a long row
+    const gptr<const T> p = base + item * kFlagChunk;   // chunks of the rows in order
+    vec v[kL];
+#pragma unroll
+    for (int u = 0; u < kL; ++u) v[u] = *(gptr<const vec>)(p + (u * 64 + lane) * kV);
+    int any = 0;
+#pragma unroll
+    for (int u = 0; u < kL; ++u)
+#pragma unroll
+      for (int e = 0; e < kV; ++e) any |= v[u][e] != T(0);
+    any = __any(any);
+    if (lane == 0) flags[item] = any;
+    return;
+  }
+  // rows r0 .. of a run: element (u 64 + lane) kV + e of it
+  const int64_t r0 = item * flag_rows(d.cols);
+  const int64_t left = (d.rows - r0) * d.cols;   // a multiple of kV
+  vec v[kL];
+#pragma unroll
+  for (int u = 0; u < kL; ++u) {
+    const int64_t e = (int64_t)(u * 64 + lane) * kV;
+    v[u] = e < left ? *(gptr<const vec>)(base + r0 * d.cols + e) : vec{};
+  }
+  const int per = (int)(d.cols / kV);   // vectors per row, a power of two
+  unsigned long long acc = 0;           // rows that span several loads
+#pragma unroll
+  for (int u = 0; u < kL; ++u) {
+    int any = 0;
+#pragma unroll
+    for (int e = 0; e < kV; ++e) any |= v[u][e] != T(0);
+    const unsigned long long bal = __ballot(any);
+    if (per >= 64) {
+      acc |= bal;
+      if ((u * 64 + 64) % per == 0) {
+        const int64_t r = r0 + (u * 64) / per;
+        if (lane == 0 && r < d.rows) flags[r] = acc != 0;
+        acc = 0;
       }
     } else {
-      for (int64_t c = c0 + threadIdx.x; c < c1; c += blockDim.x) any |= (p[c] != 0.0f);
+      const int rows = 64 / per;   // rows of this load
+      const unsigned long long mask = (1ull << per) - 1ull;
+      const int64_t r = r0 + (int64_t)u * rows + lane;
+      if (lane < rows && r < d.rows) flags[r] = ((bal >> (lane * per)) & mask) != 0;
     }
   }
-  any = __syncthreads_or(any);
-  if (threadIdx.x == 0) {
-    d.flags[rc] = any ? 1 : 0;
-    if (rc == 0 && d.unit) {
-      if (is_double) *static_cast<double *>(d.unit) = 1.0;
-      else *static_cast<float *>(d.unit) = 1.0f;
-      *d.unit_flag = 1;
-    }
+}
+
+__device__ __forceinline__ void flags_block(const FlagDesc &d, int64_t blk, bool is_double) {
+  const int64_t item = blk * 4 + uni((int32_t)(threadIdx.x >> 6));
+  if (item >= flag_items(d.rows, d.cols)) return;
+  if (is_double) flags_wave<double>(d, item);
+  else flags_wave<float>(d, item);
+  if (item == 0 && (threadIdx.x & 63) == 0 && d.unit) {
+    if (is_double) *static_cast<double *>(d.unit) = 1.0;
+    else *static_cast<float *>(d.unit) = 1.0f;
+    *d.unit_flag = 1;
   }
 }
 
@@ -619,7 +655,7 @@ __global__ __launch_bounds__(256) void k_row_flags(const FlagArgs a) {
   const int64_t bid = blockIdx.x;
   int i = 0;
   while (i + 1 < a.n && bid >= a.d[i + 1].block_start) ++i;
-  flags_chunk(a.d[i], bid - a.d[i].block_start, a.is_double != 0);
+  flags_block(a.d[i], bid - a.d[i].block_start, a.is_double != 0);
 }
 
 __global__ __launch_bounds__(256) void k_row_flags_table(const FlagDesc *descs, int32_t n, int32_t is_double,
@@ -636,7 +672,7 @@ __global__ __launch_bounds__(256) void k_row_flags_table(const FlagDesc *descs, 
     if (tab[mid].block_start <= bid) lo = mid;
     else hi = mid - 1;
   }
-  flags_chunk(descs[lo], bid - tab[lo].block_start, is_double != 0);
+  flags_block(descs[lo], bid - tab[lo].block_start, is_double != 0);
 }
 
 // One block per instance: its FP64 mass from the per-tile partials, in order.
@@ -709,7 +745,7 @@ bool tile_ok(Acc acc, int cfg) {
   return true;
 }
 
-int choose_tile(Acc acc, int nS, int logM, int logN, bool wide_ok, bool panel, int64_t nbatch) {
+int choose_tile(Acc acc, int nS, int logM, int logN, bool wide_ok, bool panel, int64_t nbatch, bool spread) {
   const int64_t M = int64_t(1) << logM, N = int64_t(1) << logN;
   if (is_split(acc)) return kTileW;
   // long term sums over large tiles are compute-bound: LDS-staged operands (or
@@ -720,9 +756,13 @@ int choose_tile(Acc acc, int nS, int logM, int logN, bool wide_ok, bool panel, i
   if (acc == Acc::F32 && (panel || (wide_ok && nS >= 3 && M >= 128 && N >= 128)) &&
       M * N * nbatch >= (int64_t(1) << 22))
     return kTileW;
-  if (M >= 64 && N >= 256) return kTileL;
+  // at least one block per CU where the step has that many outputs: 2^19 in
+  // deposit order (16 terms) took 13.5 us on 32 blocks of 64 x 256, 7.7 on
+  // 512 of 16 x 64
+  auto fills = [&](int64_t bm, int64_t bn) { return !spread || (M / bm) * (N / bn) * nbatch >= 256; };
+  if (M >= 64 && N >= 256 && fills(64, 256)) return kTileL;
   if (N < 64 && M >= 256) return kTileT;
-  if (M >= 32 && N >= 128) return kTileM;
+  if (M >= 32 && N >= 128 && fills(32, 128)) return kTileM;
   return kTileS;
 }
 

@@ -480,9 +480,34 @@ __device__ __forceinline__ void wide_run(Seq &seq) {
     const O scale = (O)sc64;
     // a run of 4 consecutive n of output row m, written element-wise (edge
     // tiles, FP64 output, bit-deposit order)
+    // the result already split into the next step's bfloat16 parts
+    const bool parts = NP > 0 && MODE == kModeIntermediate && uni(a.Zs) != nullptr;
+    auto put_parts = [&](int64_t o, const float (&w)[4], int count) {
+      const gptr<__bf16> zs = gbl(uni(static_cast<__bf16 *>(a.Zs))) + g.batch * M * N + o;
+      const int64_t plane = uni(a.zplane);
+      typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+      bf16x4 part[3];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        __bf16 x0, x1, x2;
+        split3(w[e], &x0, &x1, &x2);
+        part[0][e] = x0;
+        part[1][e] = x1;
+        part[2][e] = x2;
+      }
+#pragma unroll
+      for (int p = 0; p < (NP ? NP : 1); ++p) {
+        if (count == 4) *(gptr<bf16x4>)(zs + p * plane) = part[p];
+        else
+          for (int e = 0; e < count; ++e) zs[p * plane + e] = part[p][e];
+      }
+    };
     auto write_run = [&](int64_t m, int64_t n, const f32x4 &vals) {
       if (m >= M || n >= N) return;
-      if (MODE == kModeIntermediate) {
+      if (MODE == kModeIntermediate && parts) {
+        const float w[4] = {vals[0], vals[1], vals[2], vals[3]};
+        put_parts(m * N + n, w, N - n < 4 ? (int)(N - n) : 4);
+      } else if (MODE == kModeIntermediate) {
         const gptr<float> Z = (gptr<float>)Zb + m * N + n;
         if (n + 3 < N) *(gptr<f32x4>)Z = vals;
         else
@@ -544,6 +569,9 @@ __device__ __forceinline__ void wide_run(Seq &seq) {
             xent_put4<float>(a, o, w, c, xloss);
           }
           msum += (c[0] + c[1]) + (c[2] + c[3]);
+        } else if (MODE == kModeIntermediate && parts) {
+          const float w[4] = {v.x, v.y, v.z, v.w};
+          put_parts((m0 + row) * N + nw + c4, w, 4);
         } else {
           __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w},
                                       (gptr<f32x4>)((gptr<float>)Zb + (m0 + row) * N + nw + c4));

@@ -70,6 +70,10 @@ struct ContractArgs {
   const void *Xs;
   const void *Ys;
   int64_t xplane, yplane;
+  // split-BF16 intermediate steps whose result only a split step reads: the
+  // parts of Z are written here (part p at Zs + p * zplane elements) instead of Z
+  void *Zs;
+  int64_t zplane;
   // cross-entropy form of a final step (batched queue kernels): xt is the
   // target t in output order; every output p gets dL/dp = -t/p (0 where p <=
   // 1e-30) written to xg at its position, p itself is written only if Z is
@@ -96,9 +100,16 @@ inline size_t wide_list_bytes(int nS, int64_t nbatch) {
 // Row flags are kept per (row, chunk of kFlagChunk columns): flag[r * nch + c]
 // says whether chunk c of row r has a non-zero element; a row is live if any
 // of its chunk flags is set.  Splitting rows lets the flag pass run with many
-// small blocks instead of one block per long row.
+// waves instead of one per long row.
 constexpr int kFlagChunk = 2048;
 __host__ __device__ inline int64_t flag_chunks(int64_t cols) { return (cols + kFlagChunk - 1) / kFlagChunk; }
+// Waves of the flag pass: one per chunk of a long row, or per flag_rows() short
+// rows (cols is a power of two); four per block.
+__host__ __device__ inline int64_t flag_rows(int64_t cols) { return cols < 4 ? 64 : cols < kFlagChunk ? kFlagChunk / cols : 1; }
+__host__ __device__ inline int64_t flag_items(int64_t rows, int64_t cols) {
+  return cols >= kFlagChunk ? rows * flag_chunks(cols) : (rows + flag_rows(cols) - 1) / flag_rows(cols);
+}
+__host__ __device__ inline int64_t flag_blocks(int64_t rows, int64_t cols) { return (flag_items(rows, cols) + 3) / 4; }
 
 struct FlagDesc {
   const void *ptr;
@@ -137,7 +148,9 @@ TileShape tile_shape(int cfg);
 // nbatch: batch entries of the step (the wide kernel needs enough 128 x 128
 // tiles over all of them to fill the chip).
 // panel: the step runs on the panel kernel where its tile is W.
-int choose_tile(Acc acc, int nS, int logM, int logN, bool wide_ok, bool panel, int64_t nbatch);
+// spread: a launch of its own that writes through the register kernels (deposit
+// order, FP64, long sums): the tile shrinks until the step fills the chip.
+int choose_tile(Acc acc, int nS, int logM, int logN, bool wide_ok, bool panel, int64_t nbatch, bool spread);
 // Whether the arithmetic has a kernel with this tile configuration.
 bool tile_ok(Acc acc, int cfg);
 // Arithmetic a step of a plan runs in.  A split-form step runs the FP32 form

@@ -161,7 +161,7 @@ static Status tune_step(const NetLayout &L, size_t si, char *ws, const std::vect
     const TileShape sh = tile_shape(cfg);
     const int64_t M = int64_t(1) << st.logM, N = int64_t(1) << st.logN;
     // skip shapes that would leave most of every tile empty
-    if ((M < sh.bm || N < sh.bn) && cfg != kTileS && cfg != choose_tile(sa, a.nS, st.logM, st.logN, st.wide_ok(), a.panel != 0, st.nbatch)) continue;
+    if ((M < sh.bm || N < sh.bn) && cfg != kTileS && cfg != choose_tile(sa, a.nS, st.logM, st.logN, st.wide_ok(), a.panel != 0, st.nbatch, spread_step(p, si, L.acc))) continue;
     if (cfg == kTileW && !st.wide_ok()) continue;
     a.rows = rows_cols(sa, a.mode, cfg, a.nS, st.logM, st.logN);
     for (int xcd = 0; xcd < 2; ++xcd) {
