@@ -98,6 +98,8 @@ class FDCall:
     buffers allocated once; run() enqueues the whole hot path on the current
     stream with one library call."""
 
+    _new_mass = staticmethod(torch.zeros)
+
     def __init__(self, entries_list, cuts, precision="fp32", out_dtype=None, outs=None,
                  with_mass=True, workspace=None, noalloc=False):
         if isinstance(cuts, CutMap):
@@ -115,7 +117,7 @@ class FDCall:
         n_inst = len(self.cuts)
         self.outs = list(outs) if outs is not None else [
             torch.empty(2 ** c.n, dtype=self.out_dtype, device=dev) for c in self.cuts]
-        self.mass = torch.zeros(n_inst, dtype=torch.float64, device=dev) if with_mass else None
+        self.mass = self._new_mass(n_inst, dtype=torch.float64, device=dev) if with_mass else None
         Arr = _lib.CqcInstance * n_inst
         self._insts = Arr()
         self._keep = []
@@ -395,9 +397,14 @@ def xent_grad(p, t, grad=None, with_loss=False):
     return (grad, loss) if with_loss else grad
 
 
+class _OneShot(FDCall):
+    # run() writes the mass before anyone sees it: no kernel to clear it
+    _new_mass = staticmethod(torch.empty)
+
+
 def reconstruct_fd(entries, cut, precision="fp32", out_dtype=None, with_mass=True):
     """Full-definition reconstruction of one instance -> (p[2^n], mass or None)."""
-    call = FDCall(entries, cut, precision, out_dtype, with_mass=with_mass)
+    call = _OneShot(entries, cut, precision, out_dtype, with_mass=with_mass)
     call.run()
     return call.outs[0], (call.mass[0] if with_mass else None)
 

@@ -12,6 +12,7 @@
 #include <cstring>
 
 #include "bwd.hpp"
+#include "fdplan.hpp"
 
 namespace cqc {
 
@@ -46,19 +47,22 @@ BwdSide choose_bwd_side(int64_t inner, int64_t rest, int64_t out_elems, int64_t 
   }
 }
 
+static Status check_bwd_pointers(const cqc_instance &in, int nsub, const void *gout, void *const *gents) {
+  if (!in.entries) return Status::fail(CQC_ERR_INVALID_ARG, "entries is NULL");
+  if (!gout) return Status::fail(CQC_ERR_INVALID_ARG, "grad_out is NULL");
+  if (!gents) return Status::fail(CQC_ERR_INVALID_ARG, "grad_entries is NULL");
+  for (int c = 0; c < nsub; ++c)
+    if (!in.entries[c] || !gents[c])
+      return Status::fail(CQC_ERR_INVALID_ARG, "entry or gradient pointer " + std::to_string(c) + " is NULL");
+  return Status::ok();
+}
+
 static Status plan_bwd_instance(const cqc_instance &in, const void *gout, void *const *gents,
                                 cqc_dtype in_t, Acc acc, size_t base, bool need_ptrs,
                                 BwdInstancePlan *out) {
   BwdInstancePlan ip;
   CQC_TRY(validate_cut(&in.cut, CQC_MAX_FD_QUBITS, &ip.cut));
-  if (need_ptrs) {
-    if (!in.entries) return Status::fail(CQC_ERR_INVALID_ARG, "entries is NULL");
-    if (!gout) return Status::fail(CQC_ERR_INVALID_ARG, "grad_out is NULL");
-    if (!gents) return Status::fail(CQC_ERR_INVALID_ARG, "grad_entries is NULL");
-    for (int c = 0; c < ip.cut.nsub; ++c)
-      if (!in.entries[c] || !gents[c])
-        return Status::fail(CQC_ERR_INVALID_ARG, "entry or gradient pointer " + std::to_string(c) + " is NULL");
-  }
+  if (need_ptrs) CQC_TRY(check_bwd_pointers(in, ip.cut.nsub, gout, gents));
   std::vector<int> bitpos(ip.cut.n);
   for (int q = 0; q < ip.cut.n; ++q) bitpos[q] = ip.cut.n - 1 - q;
   Plan plan = make_plan(ip.cut, ip.cut.qubits, bitpos, ip.cut.n);
@@ -139,6 +143,35 @@ static Status bwd_plans(const cqc_instance *inst, int32_t n_inst, cqc_dtype in_t
     off = ip.end;
     plans->push_back(std::move(ip));
   }
+  return Status::ok();
+}
+
+// The plans of a call: a one-instance call takes its from the thread's memo.
+struct BwdPlans {
+  std::vector<BwdInstancePlan> own;
+  const BwdInstancePlan *one = nullptr;
+  const BwdInstancePlan &operator[](size_t i) const { return one ? *one : own[i]; }
+  size_t end() const { return one ? one->end : own.back().end; }
+};
+
+static Status bwd_call_plans(const cqc_instance *inst, int32_t n_inst, cqc_dtype in_t, cqc_precision prec,
+                             const void *const *gout, void *const *const *gents, bool need_ptrs, BwdPlans *plans,
+                             Acc *acc) {
+  static thread_local PlanMemo<BwdInstancePlan> memo;
+  PlanKey key;
+  if (inst && n_inst == 1 && (in_t == CQC_F32 || in_t == CQC_F64) && (prec == CQC_PREC_FP32 || prec == CQC_PREC_FP64) &&
+      (!need_ptrs || (gout && gents))) {
+    *acc = prec == CQC_PREC_FP64 ? Acc::F64 : Acc::F32;
+    key = plan_key(inst->cut, in_t, *acc);
+    plans->one = memo.find(key);
+    if (plans->one) {
+      const Status st = need_ptrs ? check_bwd_pointers(*inst, plans->one->cut.nsub, gout[0], gents[0]) : Status::ok();
+      if (!st.good()) set_error("instance 0: " + std::string(error_detail()));   // as bwd_plans words it
+      return st;
+    }
+  }
+  CQC_TRY(bwd_plans(inst, n_inst, in_t, prec, gout, gents, need_ptrs, &plans->own, acc));
+  if (n_inst == 1) plans->one = memo.put(key, std::move(plans->own[0]));
   return Status::ok();
 }
 
@@ -228,11 +261,11 @@ extern "C" {
 int cqc_backward_workspace_size(const cqc_instance *inst, int32_t n_inst, cqc_dtype in_t,
                                 cqc_precision prec, size_t *bytes) {
   if (!bytes) return Status::fail(CQC_ERR_INVALID_ARG, "bytes is NULL").code;
-  std::vector<BwdInstancePlan> plans;
+  BwdPlans plans;
   Acc acc;
-  Status st = bwd_plans(inst, n_inst, in_t, prec, nullptr, nullptr, false, &plans, &acc);
+  Status st = bwd_call_plans(inst, n_inst, in_t, prec, nullptr, nullptr, false, &plans, &acc);
   if (!st.good()) return st.code;
-  *bytes = plans.back().end;
+  *bytes = plans.end();
   return CQC_OK;
 }
 
@@ -240,11 +273,11 @@ int cqc_reconstruct_backward(const cqc_instance *inst, int32_t n_inst, cqc_dtype
                              cqc_precision prec, const void *const *grad_out,
                              void *const *const *grad_entries, void *workspace,
                              size_t ws_bytes, hipStream_t stream) {
-  std::vector<BwdInstancePlan> plans;
+  BwdPlans plans;
   Acc acc;
-  Status st = bwd_plans(inst, n_inst, in_t, prec, grad_out, grad_entries, true, &plans, &acc);
+  Status st = bwd_call_plans(inst, n_inst, in_t, prec, grad_out, grad_entries, true, &plans, &acc);
   if (!st.good()) return st.code;
-  const size_t need = plans.back().end;
+  const size_t need = plans.end();
   if (!workspace || ws_bytes < need)
     return Status::fail(CQC_ERR_WORKSPACE, "workspace needs " + std::to_string(need) + " bytes").code;
   if (reinterpret_cast<uintptr_t>(workspace) % 256)

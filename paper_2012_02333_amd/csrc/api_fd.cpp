@@ -22,16 +22,19 @@ Status check_dtype(cqc_dtype t) {
   return Status::ok();
 }
 
+static Status check_fd_pointers(const cqc_instance &in, int nsub, bool out_optional) {
+  if (!in.entries) return Status::fail(CQC_ERR_INVALID_ARG, "entries is NULL");
+  for (int c = 0; c < nsub; ++c)
+    if (!in.entries[c]) return Status::fail(CQC_ERR_INVALID_ARG, "entries[" + std::to_string(c) + "] is NULL");
+  if (!in.out && !out_optional) return Status::fail(CQC_ERR_INVALID_ARG, "out is NULL");
+  return Status::ok();
+}
+
 Status plan_fd_instance(const cqc_instance &in, cqc_dtype in_t, Acc acc, size_t base,
                                bool need_ptrs, FdInstancePlan *out, bool out_optional) {
   FdInstancePlan ip;
   CQC_TRY(validate_cut(&in.cut, CQC_MAX_FD_QUBITS, &ip.cut));
-  if (need_ptrs) {
-    if (!in.entries) return Status::fail(CQC_ERR_INVALID_ARG, "entries is NULL");
-    for (int c = 0; c < ip.cut.nsub; ++c)
-      if (!in.entries[c]) return Status::fail(CQC_ERR_INVALID_ARG, "entries[" + std::to_string(c) + "] is NULL");
-    if (!in.out && !out_optional) return Status::fail(CQC_ERR_INVALID_ARG, "out is NULL");
-  }
+  if (need_ptrs) CQC_TRY(check_fd_pointers(in, ip.cut.nsub, out_optional));
   std::vector<int> bitpos(ip.cut.n);
   for (int q = 0; q < ip.cut.n; ++q) bitpos[q] = ip.cut.n - 1 - q;
   Plan plan = make_plan(ip.cut, ip.cut.qubits, bitpos, ip.cut.n);
@@ -77,6 +80,25 @@ Status fd_plans(const cqc_instance *inst, int32_t n_inst, cqc_dtype in_t, cqc_dt
   return Status::ok();
 }
 
+Status fd_plan_one(const cqc_instance &in, cqc_dtype in_t, cqc_dtype out_t, cqc_precision prec, bool need_ptrs,
+                   const FdInstancePlan **plan, Acc *acc_out) {
+  static thread_local PlanMemo<FdInstancePlan> memo;
+  CQC_TRY(check_dtype(in_t));
+  CQC_TRY(check_dtype(out_t));
+  CQC_TRY(precision_acc(prec, acc_out));
+  const PlanKey key = plan_key(in.cut, in_t, *acc_out);
+  *plan = memo.find(key);
+  if (*plan) {
+    const Status st = need_ptrs ? check_fd_pointers(in, (*plan)->cut.nsub, false) : Status::ok();
+    if (!st.good()) set_error("instance 0: " + std::string(error_detail()));   // as fd_plans words it
+    return st;
+  }
+  std::vector<FdInstancePlan> plans;
+  CQC_TRY(fd_plans(&in, 1, in_t, out_t, prec, need_ptrs, &plans, acc_out));
+  *plan = memo.put(key, std::move(plans[0]));
+  return Status::ok();
+}
+
 size_t batch_workspace_bytes(const cqc_instance *inst, int32_t n_inst, cqc_dtype in_t, cqc_dtype out_t,
                              cqc_precision prec, Status *st);
 
@@ -89,8 +111,14 @@ extern "C" {
 int cqc_fd_workspace_size(const cqc_instance *inst, int32_t n_inst, cqc_dtype in_t,
                           cqc_dtype out_t, cqc_precision prec, size_t *bytes) {
   if (!bytes) return Status::fail(CQC_ERR_INVALID_ARG, "bytes is NULL").code;
-  std::vector<FdInstancePlan> plans;
   Acc acc;
+  if (inst && n_inst == 1) {
+    const FdInstancePlan *ip = nullptr;
+    const Status s1 = fd_plan_one(*inst, in_t, out_t, prec, false, &ip, &acc);
+    if (s1.good()) *bytes = ip->end;
+    return s1.code;
+  }
+  std::vector<FdInstancePlan> plans;
   Status st = fd_plans(inst, n_inst, in_t, out_t, prec, false, &plans, &acc);
   if (!st.good()) return st.code;
   *bytes = plans.back().end;
@@ -106,10 +134,12 @@ int cqc_reconstruct_fd(const cqc_instance *inst, int32_t n_inst, cqc_dtype in_t,
                        cqc_dtype out_t, cqc_precision prec, void *workspace,
                        size_t ws_bytes, hipStream_t stream) {
   std::vector<FdInstancePlan> plans;
+  const FdInstancePlan *one = nullptr;
   Acc acc;
-  Status st = fd_plans(inst, n_inst, in_t, out_t, prec, true, &plans, &acc);
+  Status st = inst && n_inst == 1 ? fd_plan_one(*inst, in_t, out_t, prec, true, &one, &acc)
+                                  : fd_plans(inst, n_inst, in_t, out_t, prec, true, &plans, &acc);
   if (!st.good()) return st.code;
-  const size_t need = plans.back().end;
+  const size_t need = one ? one->end : plans.back().end;
   if (!workspace && need > 0) return Status::fail(CQC_ERR_WORKSPACE, "workspace is NULL").code;
   if (ws_bytes < need)
     return Status::fail(CQC_ERR_WORKSPACE, "workspace has " + std::to_string(ws_bytes) +
@@ -128,7 +158,7 @@ int cqc_reconstruct_fd(const cqc_instance *inst, int32_t n_inst, cqc_dtype in_t,
     return rc;
   }
   for (int32_t i = 0; i < n_inst; ++i) {
-    const FdInstancePlan &ip = plans[i];
+    const FdInstancePlan &ip = one ? *one : plans[i];
     std::vector<const void *> ents(ip.cut.nsub);
     for (int c = 0; c < ip.cut.nsub; ++c) {
       if (in_double != acc_double) {
