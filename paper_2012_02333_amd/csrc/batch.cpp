@@ -160,7 +160,8 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
       a.nblocks = (int64_t)a.tilesM * a.tilesN * st.nbatch;
       a.mx = to_dev(st.mx);
       a.my = to_dev(st.my);
-      a.rows = rows_cols(step_acc(B.acc, st.wide_ok(), a.nS), step_mode, cfg, a.nS, st.logM, st.logN);
+      a.rows = rows_cols(step_acc(B.acc, st.wide_ok(), a.nS), step_mode, cfg, a.nS, st.logM, st.logN,
+                         2 * (a.nRX + a.nRY));
       set_lists(L, s, ws, &a);
       const Acc sa = step_acc(B.acc, st.wide_ok(), (int)st.S.size());
       a.panel = cfg == kTileW && sa == Acc::F32 && panel_step(p, s) ? 1 : 0;

@@ -217,9 +217,15 @@ __host__ __device__ inline int panel_queue_log_tiles(int logM) {
 // runs on it, or 0.  FP32 steps of at most two shared cuts, output not in
 // deposit order, whole 16-row tiles, and the widest panel (64 columns per lane
 // column) of the tile shape the step was given - so a tuned narrower tile
-// keeps the register kernel it was timed with.
-inline int rows_cols(Acc acc, int mode, int cfg, int nS, int logM, int logN) {
-  if (acc != Acc::F32 || mode == kModeFinalDeposit || nS > 2 || logM < 4 || logN < 6) return 0;
+// keeps the register kernel it was timed with.  Steps under 2^kRowsMinLog
+// outputs (all batch entries) stay there too: the time is the launch's either
+// way, and in a batch every kind of step is a launch (seven instances of 10 to
+// 12 qubits: 83 us per training step with these steps in one launch, 86 split).
+constexpr int kRowsMinLog = 14;
+inline int rows_cols(Acc acc, int mode, int cfg, int nS, int logM, int logN, int log_batch) {
+  if (acc != Acc::F32 || mode == kModeFinalDeposit || nS > 2 || logM < 4 || logN < 6 ||
+      logM + logN + log_batch < kRowsMinLog)
+    return 0;
   const int c = logN >= 8 ? 4 : logN == 7 ? 2 : 1;
   switch (cfg) {
     case kTileL: return c == 4 ? 4 : 0;
