@@ -206,7 +206,8 @@ Status run_net(const NetLayout &L, char *ws, const std::vector<const void *> &en
       // kernel's units of one row run
       xcd = cfg == kTileW ? 1 : 0;
     }
-    a.rows = rows_cols(sa, mode, cfg, a.nS, st.logM, st.logN, 2 * (a.nRX + a.nRY));
+    a.rows = sa == Acc::F64 ? (od ? rows_cols_f64(mode, cfg, a.nS, st.logM, st.logN, 2 * (a.nRX + a.nRY)) : 0)
+                            : rows_cols(sa, mode, cfg, a.nS, st.logM, st.logN, 2 * (a.nRX + a.nRY));
     const TileShape sh = tile_shape(cfg);
     a.tilesM = (int)(((int64_t(1) << st.logM) + sh.bm - 1) / sh.bm);
     a.tilesN = (int)(((int64_t(1) << st.logN) + sh.bn - 1) / sh.bn);

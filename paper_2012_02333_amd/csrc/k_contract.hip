@@ -127,13 +127,13 @@ __device__ __forceinline__ void contract_tile(const ContractArgs &a, uint32_t bl
       coloff[c] = (int64_t)tn * BN + c < N ? deposit((int64_t)tn * BN + c, a.posY, a.logN) : 0;
   }
 
-  // column offsets of this lane's operands (masked where the tile overhangs)
+  // column offsets of this lane's operands; where the tile overhangs, column 0
+  // (an output depends on its own row and column only, and those are not written)
   int64_t xcol[BMB], ycol[BNB];
-  bool xok[BMB], yok[BNB];
 #pragma unroll
-  for (int i = 0; i < BMB; ++i) { xcol[i] = mw + i * 16 + l16; xok[i] = xcol[i] < M; }
+  for (int i = 0; i < BMB; ++i) { const int64_t c = mw + i * 16 + l16; xcol[i] = c < M ? c : 0; }
 #pragma unroll
-  for (int j = 0; j < BNB; ++j) { ycol[j] = nw + j * 16 + l16; yok[j] = ycol[j] < N; }
+  for (int j = 0; j < BNB; ++j) { const int64_t c = nw + j * 16 + l16; ycol[j] = c < N ? c : 0; }
 
   V acc[BMB][BNB];
 #pragma unroll
@@ -169,15 +169,26 @@ __device__ __forceinline__ void contract_tile(const ContractArgs &a, uint32_t bl
       T bx[KG][BMB], ay[KG][BNB];
 #pragma unroll
       for (int q = 0; q < KG; ++q) {
+        // every load is made (row 0 past the live terms) and the missing terms
+        // are zeroed afterwards: a masked load is a branch and a wait each
         const int2 rr = lst[k0 + 4 * q + lg];
         const bool kok = rr.x >= 0;
-        const T *xr = X + (int64_t)(kok ? rr.x : 0) * M;
-        const T *yr = Y + (int64_t)(kok ? rr.y : 0) * N;
+        const gptr<const T> xr = gbl(X) + (int64_t)(kok ? rr.x : 0) * M;
+        const gptr<const T> yr = gbl(Y) + (int64_t)(kok ? rr.y : 0) * N;
 #pragma unroll
-        for (int i = 0; i < BMB; ++i) bx[q][i] = (kok && xok[i]) ? xr[xcol[i]] : (T)0;
+        for (int i = 0; i < BMB; ++i) bx[q][i] = xr[xcol[i]];
 #pragma unroll
-        for (int j = 0; j < BNB; ++j) ay[q][j] = (kok && yok[j]) ? yr[ycol[j]] : (T)0;
+        for (int j = 0; j < BNB; ++j) ay[q][j] = yr[ycol[j]];
       }
+      if (k0 + 4 * KG > cnt)
+#pragma unroll
+        for (int q = 0; q < KG; ++q) {
+          const bool kok = lst[k0 + 4 * q + lg].x >= 0;
+#pragma unroll
+          for (int i = 0; i < BMB; ++i) bx[q][i] = kok ? bx[q][i] : (T)0;
+#pragma unroll
+          for (int j = 0; j < BNB; ++j) ay[q][j] = kok ? ay[q][j] : (T)0;
+        }
 #pragma unroll
       for (int q = 0; q < KG; ++q)
 #pragma unroll
@@ -351,18 +362,29 @@ __device__ __forceinline__ void contract_small_tile(const ContractArgs &a, uint3
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const bool kok = rrq[q].x >= 0;
-      const T *yr = Y + (int64_t)(kok ? rrq[q].y : 0) * N;
-      const T *xr = X + (int64_t)(kok ? rrq[q].x : 0) * M;
+      const gptr<const T> yr = gbl(Y) + (int64_t)(kok ? rrq[q].y : 0) * N;
+      const gptr<const T> xr = gbl(X) + (int64_t)(kok ? rrq[q].x : 0) * M;
+      // unconditional loads (column 0 where the tile overhangs), as in contract_tile
 #pragma unroll
       for (int j = 0; j < BNB; ++j) {
         const int64_t c = nw + j * 16 + l16;
-        ay[q][j] = (kok && c < N) ? yr[c] : (T)0;
+        ay[q][j] = yr[c < N ? c : 0];
       }
 #pragma unroll
       for (int i = 0; i < BMB; ++i) {
         const int64_t c = mw + i * 16 + l16;
-        bxa[i][q] = (kok && c < M) ? xr[c] : (T)0;
+        bxa[i][q] = xr[c < M ? c : 0];
       }
+    }
+  };
+  auto zero_missing = [&]() {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bool kok = rrq[q].x >= 0;
+#pragma unroll
+      for (int j = 0; j < BNB; ++j) ay[q][j] = kok ? ay[q][j] : (T)0;
+#pragma unroll
+      for (int i = 0; i < BMB; ++i) bxa[i][q] = kok ? bxa[i][q] : (T)0;
     }
   };
   load_ops();
@@ -389,6 +411,7 @@ __device__ __forceinline__ void contract_small_tile(const ContractArgs &a, uint3
     for (int q = 0; q < 4; ++q) rrq[q] = lst[4 * q + lg];
     load_ops();
   }
+  if (cnt_sh < 16) zero_missing();
 
   double msum = 0.0;
   const O scale = (O)a.scale;
@@ -577,7 +600,6 @@ __global__ __launch_bounds__(256) void k_contract_queue(const ContractArgs *desc
 template <typename T>
 __device__ __forceinline__ void flags_wave(const FlagDesc &d, int64_t item) {
   const int lane = threadIdx.x & 63;
-  const int64_t nch = flag_chunks(d.cols);
   const gptr<const T> base = gbl(static_cast<const T *>(d.ptr));
   const gptr<int32_t> flags = gbl(d.flags);
   constexpr int kV = 16 / sizeof(T), kL = kFlagChunk / (64 * kV);   // elements per load, loads per lane
@@ -591,11 +613,15 @@ __device__ __forceinline__ void flags_wave(const FlagDesc &d, int64_t item) {
     }
     return;
   }
-  if (nch > 1 || d.cols == kFlagChunk) {   // a chunk of a long row
-    const gptr<const T> p = base + item * kFlagChunk;   // chunks of the rows in order
+  if (d.cols > kFlagRun) {   // a chunk of a long row
+    const int len = (int)(d.cols < kFlagChunk ? d.cols : kFlagChunk);
+    const gptr<const T> p = base + item * len;   // chunks of the rows in order
     vec v[kL];
 #pragma unroll
-    for (int u = 0; u < kL; ++u) v[u] = *(gptr<const vec>)(p + (u * 64 + lane) * kV);
+    for (int u = 0; u < kL; ++u) {
+      const int e = (u * 64 + lane) * kV;
+      v[u] = u * 64 * kV < len ? *(gptr<const vec>)(p + e) : vec{};   // len is a multiple of a whole wave load
+    }
     int any = 0;
 #pragma unroll
     for (int u = 0; u < kL; ++u)
@@ -608,16 +634,17 @@ __device__ __forceinline__ void flags_wave(const FlagDesc &d, int64_t item) {
   // rows r0 .. of a run: element (u 64 + lane) kV + e of it
   const int64_t r0 = item * flag_rows(d.cols);
   const int64_t left = (d.rows - r0) * d.cols;   // a multiple of kV
-  vec v[kL];
+  constexpr int kR = kFlagRun / (64 * kV);
+  vec v[kR];
 #pragma unroll
-  for (int u = 0; u < kL; ++u) {
+  for (int u = 0; u < kR; ++u) {
     const int64_t e = (int64_t)(u * 64 + lane) * kV;
     v[u] = e < left ? *(gptr<const vec>)(base + r0 * d.cols + e) : vec{};
   }
   const int per = (int)(d.cols / kV);   // vectors per row, a power of two
   unsigned long long acc = 0;           // rows that span several loads
 #pragma unroll
-  for (int u = 0; u < kL; ++u) {
+  for (int u = 0; u < kR; ++u) {
     int any = 0;
 #pragma unroll
     for (int e = 0; e < kV; ++e) any |= v[u][e] != T(0);
@@ -832,7 +859,7 @@ static Status launch_contract_t(int cfg, const ContractArgs &a, hipStream_t s) {
 
 Status launch_contract(Acc acc, bool out_double, int cfg, const ContractArgs &a, hipStream_t s) {
   if (!tile_ok(acc, cfg)) return Status::fail(CQC_ERR_INVALID_ARG, "tile configuration not available for this arithmetic");
-  if (acc == Acc::F32 && a.rows) return launch_rows(out_double, a, s);
+  if (a.rows) return acc == Acc::F32 ? launch_rows(out_double, a, s) : launch_rows_f64(a, s);
   if (cfg == kTileW) return launch_contract_wide(split_parts(acc), out_double, a, s);
   if (acc == Acc::F32)
     return out_double ? launch_contract_t<float, double>(cfg, a, s)

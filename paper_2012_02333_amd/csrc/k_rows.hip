@@ -283,6 +283,96 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NS == 2 ? 3
   else rows_unit<float, MODE, XE, XE == 0, C, NS>(a, lt, unit);
 }
 
+// The FP64 form (FP64 output, single calls): 16 rows by 128 columns per tile on
+// v_mfma_f64_16x16x4_f64, the same products in the same order as the register
+// kernel, so the same bits.  The even and odd columns of 32 sit in two products:
+// a lane's pair of accumulators is 16 adjacent bytes, and one instruction
+// writes 256 contiguous bytes of four rows (128 from the register kernel, which
+// also loads Y again for every 64 rows).  2^25 outputs of 16 terms: 54 us there
+// (5.0 TB/s), F64_US here; a fill of that size takes 39.
+template <int MODE, int NS>
+__device__ __forceinline__ void rows64_unit(const ContractArgs &a, int lt, int64_t unit) {
+  constexpr int K = 1 << (2 * NS), NQ = K >= 4 ? K / 4 : 1, NB = 8;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
+  const int logM = uni(a.logM), logN = uni(a.logN);
+  const int lp = logN - 7, lr = logM - 4 - lt;
+  const int64_t batch = unit >> (lp + lr);
+  if (batch >= a.nbatch) return;
+  const int64_t n0 = (unit & ((int64_t(1) << lp) - 1)) << 7;
+  const int64_t m0 = ((unit >> lp) & ((int64_t(1) << lr) - 1)) << (4 + lt);
+  const int rX = (int)(batch >> (2 * a.nRY)), rY = (int)(batch & ((int64_t(1) << (2 * a.nRY)) - 1));
+  // rows of the operands: lane t < K computes those of term t, and whether it is live
+  const int rx = lane < K ? row_of(a.mx, lane, rX) : 0, ry = lane < K ? row_of(a.my, lane, rY) : 0;
+  uint32_t live = (1u << K) - 1u;
+  if (uni(a.flagX) != nullptr)
+    live = (uint32_t)__ballot(lane < K && (row_live(a.flagX, a.nchX, rx) & row_live(a.flagY, a.nchY, ry)));
+  const gptr<const double> Xb = gbl(static_cast<const double *>(uni(a.X))), Yb = gbl(static_cast<const double *>(uni(a.Y)));
+  typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+  double y[NQ][NB], x[NQ];
+  gptr<const double> xp[NQ];
+  bool ok[NQ];   // this lane's term of the quad is live
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int t = 4 * q + lg, ts = t < K ? t : 0;
+    ok[q] = t < K && ((live >> ts) & 1u);
+    const gptr<const double> yr = Yb + ((int64_t)__shfl(ry, ts, 64) << logN) + n0 + 2 * l16;
+#pragma unroll
+    for (int p = 0; p < NB / 2; ++p) {
+      const d2 v = *(gptr<const d2>)(yr + 32 * p);
+      y[q][2 * p] = v[0];
+      y[q][2 * p + 1] = v[1];
+    }
+    xp[q] = Xb + ((int64_t)__shfl(rx, ts, 64) << logM) + m0 + l16;
+    x[q] = *xp[q];
+  }
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) y[q][j] = ok[q] ? y[q][j] : 0.0;
+  const double sc = MODE == kModeIntermediate ? 1.0 : uni(a.scale);
+  gptr<double> Z = gbl(static_cast<double *>(uni(a.Z))) + (MODE == kModeIntermediate ? batch << (logM + logN) : 0) +
+                   ((m0 + lg) << logN) + n0 + 2 * l16;
+  double msum = 0.0;
+  const int tiles = 1 << lt;
+  for (int it = 0; it < tiles; ++it) {
+    double xv[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      xv[q] = ok[q] ? x[q] : 0.0;
+      if (it + 1 < tiles) xp[q] += 16;   // the last tile reloads itself
+      x[q] = *xp[q];
+    }
+#pragma unroll
+    for (int p = 0; p < NB / 2; ++p) {
+      f64x4 e{0, 0, 0, 0}, o{0, 0, 0, 0};
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        e = MfmaOp<double>::run(xv[q], y[q][2 * p], e);
+        o = MfmaOp<double>::run(xv[q], y[q][2 * p + 1], o);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const d2 v = {e[r] * sc, o[r] * sc};
+        __builtin_nontemporal_store(v, (gptr<d2>)(Z + ((int64_t)(4 * r) << logN) + 32 * p));
+        if (MODE != kModeIntermediate) msum += v[0] + v[1];
+      }
+    }
+    Z += int64_t(16) << logN;
+  }
+  if (MODE == kModeIntermediate) {
+    if (a.flagZ && lane == 0 && (unit & ((int64_t(1) << (lp + lr)) - 1)) == 0) gbl(a.flagZ)[batch] = live != 0;
+  } else if (a.partials) {
+    const double tot = wave_sum_f64(msum);
+    if (lane == 0) gbl(a.partials)[unit] = tot;
+  }
+}
+
+template <int MODE, int NS>
+__global__ __launch_bounds__(256) void k_rows_f64(const ContractArgs a, int lt) {
+  if (gated_off(a.gate, a.gate_val)) return;
+  rows64_unit<MODE, NS>(a, lt, (int64_t)blockIdx.x * 4 + uni((int32_t)(threadIdx.x >> 6)));
+}
+
 int64_t rows_units(const ContractArgs &a) {
   const int lt = rows_log_tiles(a.logM, a.logN, 2 * (a.nRX + a.nRY), a.rows, a.nS);
   return a.nbatch << (a.logM - 4 - lt + a.logN - 6 - (a.rows == 4 ? 2 : a.rows == 2 ? 1 : 0));
@@ -314,6 +404,24 @@ Status launch_rows(bool out_double, const ContractArgs &a, hipStream_t s) {
     return Status::fail(CQC_ERR_INVALID_ARG, "row contraction: step shape");
   if (a.mode == kModeIntermediate) return launch_rows_m<float, kModeIntermediate>(a, s);
   return out_double ? launch_rows_m<double, kModeFinalBlocked>(a, s) : launch_rows_m<float, kModeFinalBlocked>(a, s);
+}
+
+template <int MODE>
+static Status launch_rows_f64_m(const ContractArgs &a, hipStream_t s) {
+  const int lt = rows_log_tiles(a.logM, a.logN, 2 * (a.nRX + a.nRY), a.rows, a.nS);
+  const dim3 grid((unsigned)((rows_units(a) + 3) / 4)), block(256);
+  const char *nm = "contract_small_64x256";   // the register kernel's name: its FP64 form
+  switch (a.nS) {
+    case 0: return launch(nm, k_rows_f64<MODE, 0>, grid, block, 0, s, a, lt);
+    case 1: return launch(nm, k_rows_f64<MODE, 1>, grid, block, 0, s, a, lt);
+    default: return launch(nm, k_rows_f64<MODE, 2>, grid, block, 0, s, a, lt);
+  }
+}
+
+Status launch_rows_f64(const ContractArgs &a, hipStream_t s) {
+  if (a.rows != 2 || a.nS > 2 || a.logM < 4 || a.logN < 7 || a.mode == kModeFinalDeposit)
+    return Status::fail(CQC_ERR_INVALID_ARG, "row contraction: step shape");
+  return a.mode == kModeIntermediate ? launch_rows_f64_m<kModeIntermediate>(a, s) : launch_rows_f64_m<kModeFinalBlocked>(a, s);
 }
 
 template <int MODE, int XE, int C>

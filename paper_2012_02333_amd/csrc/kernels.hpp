@@ -103,11 +103,14 @@ inline size_t wide_list_bytes(int nS, int64_t nbatch) {
 // waves instead of one per long row.
 constexpr int kFlagChunk = 2048;
 __host__ __device__ inline int64_t flag_chunks(int64_t cols) { return (cols + kFlagChunk - 1) / kFlagChunk; }
-// Waves of the flag pass: one per chunk of a long row, or per flag_rows() short
-// rows (cols is a power of two); four per block.
-__host__ __device__ inline int64_t flag_rows(int64_t cols) { return cols < 4 ? 64 : cols < kFlagChunk ? kFlagChunk / cols : 1; }
+// Waves of the flag pass: one per chunk of a row longer than kFlagRun columns,
+// or per flag_rows() shorter rows (cols is a power of two); four per block.
+// Runs of 2048 columns left too few waves for small tensors (282 K doubles: 7.5
+// us, against 5.2 with a block per row), runs of 512 do not.
+constexpr int kFlagRun = 512;
+__host__ __device__ inline int64_t flag_rows(int64_t cols) { return cols < 4 ? 64 : cols <= kFlagRun ? kFlagRun / cols : 1; }
 __host__ __device__ inline int64_t flag_items(int64_t rows, int64_t cols) {
-  return cols >= kFlagChunk ? rows * flag_chunks(cols) : (rows + flag_rows(cols) - 1) / flag_rows(cols);
+  return cols > kFlagRun ? rows * flag_chunks(cols) : (rows + flag_rows(cols) - 1) / flag_rows(cols);
 }
 __host__ __device__ inline int64_t flag_blocks(int64_t rows, int64_t cols) { return (flag_items(rows, cols) + 3) / 4; }
 
@@ -234,6 +237,11 @@ inline int rows_cols(Acc acc, int mode, int cfg, int nS, int logM, int logN, int
     default: return 0;
   }
 }
+// The same for the FP64 form of a single call with FP64 output: 2 (128 columns) or 0.
+inline int rows_cols_f64(int mode, int cfg, int nS, int logM, int logN, int log_batch) {
+  return (cfg == kTileL || cfg == kTileM) && mode != kModeFinalDeposit && nS <= 2 && logM >= 4 && logN >= 7 &&
+         logM + logN + log_batch >= kRowsMinLog ? 2 : 0;
+}
 // 16-row tiles per wave (log2).  Longer runs reload Y less often, but spread
 // the rows that the chip writes at one time over more memory: two tiles at 16
 // terms as long as that leaves 2048 waves (2^11 x 2^13 outputs: 17.0, 14.8,
@@ -250,6 +258,7 @@ __host__ __device__ inline int rows_log_tiles(int logM, int logN, int log_batch,
 // Waves of a step: one FP64 partial each in a final step, four per block.
 int64_t rows_units(const ContractArgs &a);
 Status launch_rows(bool out_double, const ContractArgs &a, hipStream_t s);
+Status launch_rows_f64(const ContractArgs &a, hipStream_t s);
 // Many steps of equal rows and nS: prefix[d] = first block of step d.
 Status launch_rows_table(int mode, int rows, int nS, const QueueLaunch &q, hipStream_t s);
 // FP64 partials of a final step's launch (queue launch) with tile cfg.

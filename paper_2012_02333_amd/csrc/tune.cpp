@@ -163,7 +163,8 @@ static Status tune_step(const NetLayout &L, size_t si, char *ws, const std::vect
     // skip shapes that would leave most of every tile empty
     if ((M < sh.bm || N < sh.bn) && cfg != kTileS && cfg != choose_tile(sa, a.nS, st.logM, st.logN, st.wide_ok(), a.panel != 0, st.nbatch, spread_step(p, si, L.acc))) continue;
     if (cfg == kTileW && !st.wide_ok()) continue;
-    a.rows = rows_cols(sa, a.mode, cfg, a.nS, st.logM, st.logN, 2 * (a.nRX + a.nRY));
+    a.rows = sa == Acc::F64 ? (od ? rows_cols_f64(a.mode, cfg, a.nS, st.logM, st.logN, 2 * (a.nRX + a.nRY)) : 0)
+                            : rows_cols(sa, a.mode, cfg, a.nS, st.logM, st.logN, 2 * (a.nRX + a.nRY));
     for (int xcd = 0; xcd < 2; ++xcd) {
       a.tilesM = (int)((M + sh.bm - 1) / sh.bm);
       a.tilesN = (int)((N + sh.bn - 1) / sh.bn);

@@ -1,4 +1,4 @@
-"""GPU parity of the row kernel (FP32 steps of at most two shared cuts): every
+"""GPU parity of the row kernels (steps of at most two shared cuts): every
 panel width (256, 128 and 64 columns) at 16 rows and above, 1, 4 and 16 terms,
 FP32 and FP64 output, dead rows where row flags are computed, batched
 intermediate steps, and the batched cross-entropy form with and without p.
@@ -10,7 +10,7 @@ import torch
 
 import workloads as W
 from oracle import fd
-from tests.gpu_util import to_dev, oracle_inputs, abs_bound, elementwise_ok, U32
+from tests.gpu_util import to_dev, oracle_inputs, abs_bound, elementwise_ok, U32, U64
 
 pytestmark = pytest.mark.gpu
 cqc = pytest.importorskip("paper_2012_02333_amd")
@@ -42,20 +42,38 @@ def test_rows_step(f, k, out):
     assert abs(float(mass) - float(p.double().sum())) <= 1e-12 * float(p.double().abs().sum())
 
 
+@pytest.mark.parametrize("k", [0, 1, 2])
+@pytest.mark.parametrize("f", [(4, 10), (6, 8), (7, 7), (9, 9)])
+def test_rows_f64_step(f, k):
+    """The FP64 form; its outputs are those of the batched register kernel bit for bit."""
+    _gpu()
+    cut = _pair(f, k)
+    host, dev = to_dev(W.random_entries(cut, seed=965 + k), torch.float64)
+    c = cqc.CutMap.from_workload(cut)
+    p, mass = cqc.reconstruct_fd(dev, c, precision="fp64")
+    ok, info = elementwise_ok(p.cpu().numpy(), fd.reconstruct(host, cut), abs_bound(host, cut), U64, 4 ** k)
+    assert ok, info
+    assert abs(float(mass) - float(p.sum())) <= 1e-12 * float(p.abs().sum())
+    batch = cqc.Batch([dev, dev], [c, c], precision="fp64")
+    batch.run()
+    assert torch.equal(batch.outs[0], p)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
 @pytest.mark.parametrize("k0,k1", [(1, 3), (2, 3), (2, 2), (3, 2)])
-def test_rows_in_chains(k0, k1):
+def test_rows_in_chains(k0, k1, prec):
     """A small-term step next to a long one (row flags, dead rows) or to
     another, as the batched intermediate or the final step."""
     _gpu()
     f = [6, 7, 6]
     cut = W.CutMap(19, f, [0] * k0 + [1] * k1, [1] * k0 + [2] * k1, list(range(19)))
     zr = [(0, 1), (2, 0), (2, 3)] + [(1, r) for r in range(4 ** (k0 + k1)) if r % 7 == 2]
-    host, dev = to_dev(W.random_entries(cut, seed=970, zero_rows=zr), torch.float32)
-    p, _ = cqc.reconstruct_fd(dev, cqc.CutMap.from_workload(cut), precision="fp32")
+    host, dev = to_dev(W.random_entries(cut, seed=970, zero_rows=zr), torch.float32 if prec == "fp32" else torch.float64)
+    p, _ = cqc.reconstruct_fd(dev, cqc.CutMap.from_workload(cut), precision=prec)
     xs = W.sample_outputs(19, 4096, seed=971)
     e64 = oracle_inputs(host)
     ok, info = elementwise_ok(p[torch.from_numpy(xs).cuda()].double().cpu().numpy(), fd.reconstruct(e64, cut, xs),
-                              abs_bound(e64, cut, xs), U32, 4 ** (k0 + k1))
+                              abs_bound(e64, cut, xs), U32 if prec == "fp32" else U64, 4 ** (k0 + k1))
     assert ok, info
 
 
