@@ -198,7 +198,7 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
           a.partials = reinterpret_cast<double *>(ws + L.partials_off);
           MassDesc md;
           md.partials = a.partials;
-          md.count = mass_partials(cfg, a, true);
+          md.count = mass_partials(cfg, a, true, false);
           md.mass = sum_to;
           B.mass.push_back(md);
         }

@@ -265,7 +265,7 @@ Status run_net(const NetLayout &L, char *ws, const std::vector<const void *> &en
       }
       if (mass) a.partials = reinterpret_cast<double *>(ws + L.partials_off);
       CQC_TRY(launch_contract(sa, out_double, cfg, a, s));
-      if (mass) CQC_TRY(launch_mass_final(a.partials, mass_partials(cfg, a, false), mass, s, gate, gate_val));
+      if (mass) CQC_TRY(launch_mass_final(a.partials, mass_partials(cfg, a, false, sa == Acc::F64), mass, s, gate, gate_val));
     }
   }
   return Status::ok();

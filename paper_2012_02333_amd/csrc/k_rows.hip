@@ -288,8 +288,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NS == 2 ? 3
 // kernel, so the same bits.  The even and odd columns of 32 sit in two products:
 // a lane's pair of accumulators is 16 adjacent bytes, and one instruction
 // writes 256 contiguous bytes of four rows (128 from the register kernel, which
-// also loads Y again for every 64 rows).  2^25 outputs of 16 terms: 54 us there
-// (5.0 TB/s), F64_US here; a fill of that size takes 39.
+// also loads Y again for every 64 rows).  2^25 outputs of 16 terms: 55 us there
+// (4.9 TB/s), 49 here (46 with ordinary stores, but the calls of a loop then
+// take 70.0 instead of 67.1 us: the write-back falls to the next kernel); a fill of that size takes 39.
 template <int MODE, int NS>
 __device__ __forceinline__ void rows64_unit(const ContractArgs &a, int lt, int64_t unit) {
   constexpr int K = 1 << (2 * NS), NQ = K >= 4 ? K / 4 : 1, NB = 8;
@@ -378,6 +379,10 @@ int64_t rows_units(const ContractArgs &a) {
   return a.nbatch << (a.logM - 4 - lt + a.logN - 6 - (a.rows == 4 ? 2 : a.rows == 2 ? 1 : 0));
 }
 
+// One tile per wave: 2^9 x 2^16 outputs of 16 terms took 48.8, 54.5, 55.5, 55.5
+// us with 1, 2, 4, 8 tiles.
+int64_t rows_f64_units(const ContractArgs &a) { return a.nbatch << (a.logM - 4 + a.logN - 7); }
+
 template <typename O, int MODE, int C>
 static Status launch_rows_c(const char *nm, const ContractArgs &a, hipStream_t s) {
   const int lt = rows_log_tiles(a.logM, a.logN, 2 * (a.nRX + a.nRY), a.rows, a.nS);
@@ -408,8 +413,8 @@ Status launch_rows(bool out_double, const ContractArgs &a, hipStream_t s) {
 
 template <int MODE>
 static Status launch_rows_f64_m(const ContractArgs &a, hipStream_t s) {
-  const int lt = rows_log_tiles(a.logM, a.logN, 2 * (a.nRX + a.nRY), a.rows, a.nS);
-  const dim3 grid((unsigned)((rows_units(a) + 3) / 4)), block(256);
+  const int lt = 0;
+  const dim3 grid((unsigned)((rows_f64_units(a) + 3) / 4)), block(256);
   const char *nm = "contract_small_64x256";   // the register kernel's name: its FP64 form
   switch (a.nS) {
     case 0: return launch(nm, k_rows_f64<MODE, 0>, grid, block, 0, s, a, lt);

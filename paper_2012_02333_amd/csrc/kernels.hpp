@@ -257,13 +257,14 @@ __host__ __device__ inline int rows_log_tiles(int logM, int logN, int log_batch,
 }
 // Waves of a step: one FP64 partial each in a final step, four per block.
 int64_t rows_units(const ContractArgs &a);
+int64_t rows_f64_units(const ContractArgs &a);
 Status launch_rows(bool out_double, const ContractArgs &a, hipStream_t s);
 Status launch_rows_f64(const ContractArgs &a, hipStream_t s);
 // Many steps of equal rows and nS: prefix[d] = first block of step d.
 Status launch_rows_table(int mode, int rows, int nS, const QueueLaunch &q, hipStream_t s);
 // FP64 partials of a final step's launch (queue launch) with tile cfg.
-inline int64_t mass_partials(int cfg, const ContractArgs &a, bool queue) {
-  if (a.rows) return rows_units(a);
+inline int64_t mass_partials(int cfg, const ContractArgs &a, bool queue, bool f64) {
+  if (a.rows) return f64 ? rows_f64_units(a) : rows_units(a);
   return cfg == kTileW && a.panel ? panel_partials(a, queue) : kPartialsPerTile * a.nblocks;
 }
 // Splits `count` floats (a multiple of 4) into `parts` bfloat16 planes of
