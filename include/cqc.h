@@ -138,10 +138,9 @@ int cqc_reconstruct_fd_noalloc(const cqc_instance *inst, int32_t n_inst, cqc_dty
 /* Prepared batches (the batched form of cqc_reconstruct_fd).  A batch of
  * independent instances of uneven n and K is reconstructed by a fixed, small
  * number of kernel launches: one row-flag pass over every entry tensor, one
- * persistent launch per group of contraction steps of equal kernel shape (all
- * instances' intermediate contractions first, then all final ones, each
- * group drained from a cost-ordered work queue) and one pass for every FP64
- * mass.
+ * launch per group of contraction steps of equal kernel shape (all instances'
+ * intermediate contractions first, then all final ones, each group's steps
+ * most expensive first) and one pass for every FP64 mass.
  * cqc_batch_create validates and plans the batch (n_inst >= 2, else
  * CQC_ERR_INVALID_ARG), writes its descriptor tables into `workspace` (at
  * least cqc_fd_workspace_size() bytes for the same instances, which must stay

@@ -117,3 +117,35 @@ def test_panel_batch_xent(keep, loss):
             assert abs(float(batch.losses[i]) + float(term.sum())) <= 2.0 ** -22 * float(term.abs().sum()), i
         else:
             assert abs(float(batch.mass[i]) - float(p.double().sum())) <= 1e-12 * float(p.double().abs().sum()), i
+
+
+@pytest.mark.parametrize("f,k", [((10, 10), 1), ((10, 10), 2), ((10, 12), 3), ((10, 12), 4)])
+def test_outputs_and_targets_at_4_byte_alignment(f, k):
+    """Row, panel and stream kernels with every caller buffer one element past
+    its alignment: the outputs and gradients of aligned buffers, bit for bit,
+    and nothing written before or after."""
+    _gpu()
+    n = sum(f)
+    cut_w = W.CutMap(n, list(f), [0] * k, [1] * k, list(range(n)))
+    cut = cqc.CutMap.from_workload(cut_w)
+    dev = to_dev([np.abs(E) for E in W.random_entries(cut_w, seed=1200 + k)], torch.float32)[1]
+
+    def shifted(x):
+        buf = torch.full((x.numel() + 2,), 7.0, device="cuda")
+        buf[1:-1].copy_(x.reshape(-1))
+        return buf, buf[1:-1].view(x.shape)
+
+    t = torch.from_numpy(W.dirichlet_target(n, 1210).astype(np.float32)).cuda()
+    ents = [shifted(E)[1] for E in dev]
+    bo, out = shifted(torch.zeros(2 ** n, device="cuda"))
+    bg, grad = shifted(torch.zeros(2 ** n, device="cuda"))
+    call = cqc.FDCall(ents, cut, "fp32", outs=[out])
+    call.run()
+    p, mass = cqc.reconstruct_fd(dev, cut, precision="fp32")
+    assert torch.equal(out, p) and float(call.mass[0]) == float(mass)
+    batch = cqc.Batch([ents, ents], [cut, cut], precision="fp32", targets=[shifted(t)[1], t],
+                      grads=[grad, torch.empty_like(t)], keep_outputs=False)
+    batch.run()
+    assert torch.equal(batch.grads[0], cqc.xent_grad(p, t)) and torch.equal(batch.grads[0], batch.grads[1])
+    for b in (bo, bg):
+        assert float(b[0]) == 7.0 and float(b[-1]) == 7.0
