@@ -247,13 +247,15 @@ inline int rows_cols_f64(int mode, int cfg, int nS, int logM, int logN, int log_
 // terms as long as that leaves 2048 waves (2^11 x 2^13 outputs: 17.0, 14.8,
 // 14.8, 23 us for 1, 2, 4, 8 tiles; 2^20 x 2^10: 890, 753, 765, 808), four with
 // fewer terms as long as that leaves 1024 (2^12 x 2^12: 14.4, 14.8, 12.7, 21).
+// Rows of 2^15 columns and more are long enough by themselves (2^11 x 2^15: 47.0,
+// 56.2, 58.4 us for 1, 2, 4 tiles of 4 terms; 56.3, 60.8, 62.7 of 16).
 __host__ __device__ inline int rows_log_tiles(int logM, int logN, int log_batch, int rows, int nS) {
   const int waves = logM - 4 + logN - 6 - (rows == 4 ? 2 : rows == 2 ? 1 : 0) + log_batch;
   const int most = nS == 2 ? 1 : 2;
   int lt = waves - (nS == 2 ? 11 : 10);
   if (lt > most) lt = most;
   if (lt > logM - 4) lt = logM - 4;
-  return lt < 0 ? 0 : lt;
+  return lt < 0 || logN >= 15 ? 0 : lt;
 }
 // Waves of a step: one FP64 partial each in a final step, four per block.
 int64_t rows_units(const ContractArgs &a);
