@@ -3,10 +3,11 @@
 //
 // All steps of all instances are grouped by (plan level, kernel variant,
 // output mode, tile shape).  Intermediate levels run first, then the final
-// steps; every group is one persistent launch draining an atomic (step, tile)
-// queue whose steps are ordered most expensive first.  One launch computes the
-// entry row flags of every instance (and zeroes the queue counters), one adds
-// up every instance's FP64 mass.  The descriptor tables live in the caller's
+// steps; every group is one launch over its steps, most expensive first:
+// persistent blocks draining an atomic (step, tile) queue, or for the row
+// kernel one block per four units.  One launch computes the entry row flags of
+// every instance (and zeroes the queue counters), one adds up every instance's
+// FP64 mass.  The descriptor tables live in the caller's
 // workspace and are uploaded once by cqc_batch_create; cqc_batch_run only
 // enqueues kernels, so it can be captured in a HIP graph and replayed.
 #include <algorithm>
@@ -40,7 +41,7 @@ struct BatchBuild {
   int64_t flag_blocks = 0;
   std::vector<MassDesc> mass;
   struct G {
-    int level, mode, cfg;
+    int level, mode, cfg, counter;
     bool small, panel, stream;
     int rows, nS;
     int xent;
@@ -48,6 +49,7 @@ struct BatchBuild {
     std::vector<std::pair<double, ContractArgs>> steps;  // (cost, args)
   };
   std::vector<G> groups;
+  int n_counters = 0;   // queue launches
   size_t flag_off = 0, mass_off = 0, counter_off = 0;
   std::vector<size_t> desc_off, prefix_off, bprefix_off;
 };
@@ -206,7 +208,9 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
       const bool small = a.nS <= 2;
       // cross-entropy form of the final step: 1 gradient, 2 gradient and loss
       const int xe = xent == nullptr || !last ? 0 : (xent->losses && xent->losses[i] ? 2 : 1);
-      auto key = std::make_tuple(level, (int)a.mode, cfg, (int)small * 2 + a.panel + 64 * (a.rows ? 4 * a.rows + a.nS : 0),
+      // (the row kernel knows no tile shape: columns per lane and shared cuts tell its launches apart)
+      auto key = std::make_tuple(level, (int)a.mode, a.rows ? -1 : cfg,
+                                 (int)small * 2 + a.panel + 64 * (a.rows ? 4 * a.rows + a.nS : 0),
                                  (int)sa + (a.panel && a.nS > 3 ? 64 : 0), xe);
       auto it = gidx.find(key);
       if (it == gidx.end()) {
@@ -244,17 +248,20 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
   B.mass_off = off;
   off = align_up(off + sizeof(MassDesc) * B.plans.size(), 256);   // room for every instance's mass
   B.counter_off = off;
-  off = align_up(off + sizeof(unsigned long long) * std::max<size_t>(1, B.groups.size()), 256);
+  for (auto &g : B.groups) g.counter = g.rows ? -1 : B.n_counters++;
+  off = align_up(off + sizeof(unsigned long long) * std::max(1, B.n_counters), 256);
+  // the groups' tables without gaps (their elements are 8-byte aligned): a
+  // batch of many shapes has no larger workspace than one of few
   for (auto &g : B.groups) {
     B.desc_off.push_back(off);
-    off = align_up(off + sizeof(ContractArgs) * g.steps.size(), 256);
+    off += sizeof(ContractArgs) * g.steps.size();
     B.prefix_off.push_back(off);
-    off = align_up(off + sizeof(int64_t) * (g.steps.size() + 1), 256);
+    off += sizeof(int64_t) * (g.steps.size() + 1);
     B.bprefix_off.push_back(off);
-    if (g.cfg == kTileW) off = align_up(off + sizeof(int64_t) * (g.steps.size() + 1), 256);
+    if (g.cfg == kTileW) off += sizeof(int64_t) * (g.steps.size() + 1);
   }
-  B.bytes = off;
-  if (B.groups.size() > 256)
+  B.bytes = align_up(off, 256);
+  if (B.n_counters > 256)   // the flag pass clears one per thread
     return Status::fail(CQC_ERR_UNSUPPORTED, "too many distinct step shapes in one batch");
   *out = std::move(B);
   return Status::ok();
@@ -279,14 +286,14 @@ static Status batch_run(cqc_batch_s *b, hipStream_t s) {
       }
   }
   CQC_TRY(launch_row_flags_table(b->flag_descs, b->n_flag, b->flag_blocks, acc_double, b->counters,
-                                 (int32_t)b->groups.size(), s));
+                                 b->n_counters, s));
   for (size_t g = 0; g < b->groups.size(); ++g) {
     const auto &G = b->groups[g];
     QueueLaunch q;
     q.descs = G.descs;
     q.prefix = G.prefix;
     q.ndesc = G.ndesc;
-    q.queue = b->counters + g;
+    q.queue = G.counter < 0 ? nullptr : b->counters + G.counter;
     q.total = G.total;
     q.grid = (uint32_t)std::min<int64_t>(G.total, kQueueGrid);
     q.bprefix = G.bprefix;
@@ -330,6 +337,7 @@ static Status batch_create(const cqc_instance *inst, int32_t n_inst, cqc_dtype i
   b->mass_descs = reinterpret_cast<const MassDesc *>(ws + B.mass_off);
   b->n_mass = (int32_t)B.mass.size();
   b->counters = reinterpret_cast<unsigned long long *>(ws + B.counter_off);
+  b->n_counters = B.n_counters;
   for (size_t g = 0; g < B.groups.size(); ++g) {
     const auto &G = B.groups[g];
     std::vector<ContractArgs> descs;
@@ -350,6 +358,7 @@ static Status batch_create(const cqc_instance *inst, int32_t n_inst, cqc_dtype i
     bg.level = G.level;
     bg.mode = G.mode;
     bg.cfg = G.cfg;
+    bg.counter = G.counter;
     bg.small = G.small;
     bg.rows = G.rows;
     bg.nS = G.nS;

@@ -18,8 +18,10 @@ struct cqc_batch_s {
   const cqc::MassDesc *mass_descs = nullptr;
   int32_t n_mass = 0;
   unsigned long long *counters = nullptr;
+  int32_t n_counters = 0;
   struct Group {
     int level, mode, cfg;
+    int counter;    // of the queue launches, -1 for the row kernel's
     bool small;
     int rows, nS;   // small-term steps of the row kernel: columns per lane and shared cuts
     bool panel;     // wide steps of the panel kernels

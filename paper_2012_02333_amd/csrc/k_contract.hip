@@ -592,10 +592,9 @@ __global__ __launch_bounds__(256) void k_contract_queue(const ContractArgs *desc
 
 // ---------------------------------------------------------------------------
 // Row flags of the entry tensors: whether a chunk of kFlagChunk columns of a row
-// has a non-zero element.  One wave per chunk, or per run of short rows that is
-// as long as a chunk, with all of it in flight (with a block per chunk and row
-// the 65536 rows of 512 columns of an eight-cut subcircuit took 67 us, 29
-// now).  The first wave of a tensor that carries a unit operand
+// has a non-zero element.  One wave per chunk, or per run of kFlagRun columns of
+// shorter rows, with all of it in flight (with a block per chunk and row the
+// 65536 rows of 512 columns of an eight-cut subcircuit took 67 us, 29 now).  The first wave of a tensor that carries a unit operand
 // (single-subcircuit plans) also writes that operand's value 1 and its flag.
 template <typename T>
 __device__ __forceinline__ void flags_wave(const FlagDesc &d, int64_t item) {

@@ -55,33 +55,43 @@ struct ContractArgs {
   int32_t *lists;    // [nbatch][2][list_ld] byte offsets of the live terms' X rows, then of
                      //   their Y rows, ascending s; padding 0
   int32_t *counts;   // [nbatch] live labels
-  int32_t rows;      // > 0: a small-term step that runs on the row kernel, with this many columns per lane
-  int32_t panel;     // 1: a wide step that runs on the panel kernel (every step of a queue group alike)
   int32_t list_ld;   // pairs per batch entry: 4^nS rounded up to a multiple of 32
+  int32_t rows;      // > 0: a small-term step that runs on the row kernel, with this many columns per lane
   int64_t nbatch;
   // device-side predicate: when gate is set, the launch does nothing unless
   // *gate == gate_val (a dynamic-definition query enqueues the kernels of
   // every depth a recursion can have, and runs only the one its pick chose)
   const int32_t *gate;
   int32_t gate_val;
-  // split-BF16 wide steps: the operands already split into bfloat16 parts,
-  // part p of X at Xs + p * xplane elements (same layout as X), or null (the
-  // wide kernel splits while staging)
-  const void *Xs;
-  const void *Ys;
-  int64_t xplane, yplane;
-  // split-BF16 intermediate steps whose result only a split step reads: the
-  // parts of Z are written here (part p at Zs + p * zplane elements) instead of Z
-  void *Zs;
-  int64_t zplane;
-  // cross-entropy form of a final step (batched queue kernels): xt is the
-  // target t in output order; every output p gets dL/dp = -t/p (0 where p <=
-  // 1e-30) written to xg at its position, p itself is written only if Z is
-  // set, and the partial sums add the loss terms -t log max(p, 1e-30) (kernel
-  // form with the loss) or p
-  const void *xt;
-  void *xg;
+  int32_t panel;     // 1: a wide step that runs on the panel kernel (every step of a queue group alike)
+  // A batch keeps one of these per step in the caller's workspace, whose size
+  // its users may have on record: what only single calls use and what only
+  // batches use share their place.
+  union {
+    struct {
+      // split-BF16 wide steps: the operands already split into bfloat16 parts,
+      // part p of X at Xs + p * xplane elements (same layout as X), or null (the
+      // wide kernel splits while staging)
+      const void *Xs;
+      const void *Ys;
+      int64_t xplane, yplane;
+      // split-BF16 intermediate steps whose result only a split step reads: the
+      // parts of Z are written here (part p at Zs + p * zplane elements) instead of Z
+      void *Zs;
+      int64_t zplane;
+    };
+    struct {
+      // cross-entropy form of a final step (batched launches): xt is the target
+      // t in output order; every output p gets dL/dp = -t/p (0 where p <= 1e-30)
+      // written to xg at its position, p itself is written only if Z is set, and
+      // the partial sums add the loss terms -t log max(p, 1e-30) (kernel form
+      // with the loss) or p
+      const void *xt;
+      void *xg;
+    };
+  };
 };
+static_assert(sizeof(ContractArgs) == 344, "the tables of a batch grow with it");
 
 // FP64 mass partials: every wave of a final-step tile (four per block) stores
 // the FP64 sum of the outputs it wrote at partials[kPartialsPerTile * tile +
