@@ -46,7 +46,12 @@ struct BatchBuild {
     int rows, nS;
     int xent;
     Acc acc;
-    std::vector<std::pair<double, ContractArgs>> steps;  // (cost, args)
+    struct S {
+      double cost;
+      ContractArgs args;
+      double *sum_to;   // where the FP64 sum of its partials goes, or null
+    };
+    std::vector<S> steps;
   };
   std::vector<G> groups;
   int n_counters = 0;   // queue launches
@@ -168,6 +173,7 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
       const Acc sa = step_acc(B.acc, st.wide_ok(), (int)st.S.size());
       a.panel = cfg == kTileW && sa == Acc::F32 && panel_step(p, s) ? 1 : 0;
       int level = (int)s;
+      double *sum_to = nullptr;
       if (!last) {
         a.mode = kModeIntermediate;
         a.Z = ws + L.t_off[st.z];
@@ -189,21 +195,14 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
           a.posX = pack_pos(px);
           a.posY = pack_pos(py);
         }
-        double *sum_to = need_ptrs ? inst[i].mass : nullptr;
+        sum_to = need_ptrs ? inst[i].mass : nullptr;
         if (xent && need_ptrs) {
           a.xt = xent->targets[i];
           a.xg = xent->grads[i];
           if (xent->losses && xent->losses[i]) sum_to = xent->losses[i];
         }
-        if (sum_to) {
-          // per-tile partials live in this instance's (resized) partials slot
-          a.partials = reinterpret_cast<double *>(ws + L.partials_off);
-          MassDesc md;
-          md.partials = a.partials;
-          md.count = mass_partials(cfg, a, true, false);
-          md.mass = sum_to;
-          B.mass.push_back(md);
-        }
+        // per-tile partials live in this instance's (resized) partials slot
+        if (sum_to) a.partials = reinterpret_cast<double *>(ws + L.partials_off);
       }
       const bool small = a.nS <= 2;
       // cross-entropy form of the final step: 1 gradient, 2 gradient and loss
@@ -229,17 +228,24 @@ static Status build_batch(const cqc_instance *inst, int32_t n_inst, cqc_dtype in
         B.groups.push_back(g);
       }
       const double cost = (double)a.nblocks * std::ldexp(1.0, 2 * a.nS) * sh.bm * sh.bn;
-      B.groups[it->second].steps.push_back({cost, a});
+      B.groups[it->second].steps.push_back({cost, a, sum_to});
     }
   }
   std::stable_sort(B.groups.begin(), B.groups.end(), [](const BatchBuild::G &x, const BatchBuild::G &y) {
     return x.level < y.level;
   });
-  for (auto &g : B.groups)
+  for (auto &g : B.groups) {
     std::stable_sort(g.steps.begin(), g.steps.end(),
-                     [](const std::pair<double, ContractArgs> &x, const std::pair<double, ContractArgs> &y) {
-                       return x.first > y.first;
-                     });
+                     [](const BatchBuild::G::S &x, const BatchBuild::G::S &y) { return x.cost > y.cost; });
+    if (g.panel && !g.stream) {
+      int64_t tiles = 0;
+      for (auto &st : g.steps) tiles += st.args.nbatch << (st.args.logM + st.args.logN - 12);
+      const int lt = panel_queue_log_tiles(tiles);
+      for (auto &st : g.steps) st.args.panel = 1 + std::min(lt, st.args.logM - 6);
+    }
+    for (auto &st : g.steps)
+      if (st.sum_to) B.mass.push_back(MassDesc{st.args.partials, mass_partials(g.cfg, st.args, true, false), st.sum_to});
+  }
   // tables after the instance regions
   size_t off = align_up(B.plans.back().end, 256);
   B.tables_off = off;
@@ -343,13 +349,13 @@ static Status batch_create(const cqc_instance *inst, int32_t n_inst, cqc_dtype i
     std::vector<ContractArgs> descs;
     std::vector<int64_t> prefix(1, 0), bprefix(1, 0);
     for (auto &st : G.steps) {
-      descs.push_back(st.second);
-      const int64_t nb = st.second.nblocks;
-      prefix.push_back(prefix.back() + (G.panel ? (panel_partials(st.second, true) + 3) / 4
-                                        : G.rows  ? (rows_units(st.second) + 3) / 4
+      descs.push_back(st.args);
+      const int64_t nb = st.args.nblocks;
+      prefix.push_back(prefix.back() + (G.panel ? (panel_partials(st.args, true) + 3) / 4
+                                        : G.rows  ? (rows_units(st.args) + 3) / 4
                                         : G.small ? (nb + kSmallTilesPerItem - 1) / kSmallTilesPerItem
                                                   : nb));
-      bprefix.push_back(bprefix.back() + st.second.nbatch);
+      bprefix.push_back(bprefix.back() + st.args.nbatch);
     }
     put(B.desc_off[g], descs.data(), sizeof(ContractArgs) * descs.size());
     put(B.prefix_off[g], prefix.data(), sizeof(int64_t) * prefix.size());

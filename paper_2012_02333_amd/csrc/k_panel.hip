@@ -274,8 +274,7 @@ void k_panel_queue(const ContractArgs *__restrict__ descs, const int64_t *__rest
     if (it >= total) return;
     const int d = uni(find_desc(prefix, ndesc, it));
     const ContractArgs &a = descs[d];
-    panel_unit<MODE, XE>(a, panel_queue_log_tiles(uni(a.logM)),
-                                (it - uni(prefix[d])) * 4 + uni((int32_t)(threadIdx.x >> 6)));
+    panel_unit<MODE, XE>(a, uni(a.panel) - 1, (it - uni(prefix[d])) * 4 + uni((int32_t)(threadIdx.x >> 6)));
   }
 }
 
@@ -433,7 +432,7 @@ static int panel_log_tiles(const ContractArgs &a) {
 
 int64_t panel_partials(const ContractArgs &a, bool queue) {
   if (a.nS > 3) return 4 * stream_blocks(a);
-  return a.nbatch << (a.logM + a.logN - 12 - (queue ? panel_queue_log_tiles(a.logM) : panel_log_tiles(a)));
+  return a.nbatch << (a.logM + a.logN - 12 - (queue ? a.panel - 1 : panel_log_tiles(a)));
 }
 
 // With up to this many row flags per label the waves read them themselves;

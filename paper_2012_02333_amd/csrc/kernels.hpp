@@ -63,7 +63,8 @@ struct ContractArgs {
   // every depth a recursion can have, and runs only the one its pick chose)
   const int32_t *gate;
   int32_t gate_val;
-  int32_t panel;     // 1: a wide step that runs on the panel kernel (every step of a queue group alike)
+  int32_t panel;     // > 0: a wide step that runs on the panel kernel (every step of a queue group
+                     //   alike); in a queue launch 1 + log2 of the row tiles of a unit
   // A batch keeps one of these per step in the caller's workspace, whose size
   // its users may have on record: what only single calls use and what only
   // batches use share their place.
@@ -219,12 +220,20 @@ Status launch_panel(const ContractArgs &a, hipStream_t s);
 Status launch_panel_queue(int mode, const QueueLaunch &q, hipStream_t s);
 // Their waves: four per block or queue item, one FP64 partial each in a final step.
 int64_t panel_partials(const ContractArgs &a, bool queue);
-// Row tiles per unit (log2) of a queue launch: at most 2^kPanelQueueLog, so that
-// a step of 2^19 outputs still gives 32 waves and large ones reload a panel
-// only every eighth tile.
+// Row tiles per unit (log2) of a queue launch over `tiles` 64 x 64 tiles: up to
+// 2^kPanelQueueLog, so that a panel is reloaded only every eighth tile, as long
+// as that leaves kPanelQueueUnits units, one per SIMD.  With eight tiles
+// whatever the launch, the panels of two instances of 2^20 outputs ran on 16
+// blocks: 55 us per run of that batch, 28 on the staged wide kernel before, 22
+// now; sixteen of 2^19 outputs 58.7, 43.8 and 30.7 (39.2 with 512 units at
+// least, 33.8 with 2048 or more).  The 256-instance training step takes 3.59 ms
+// with any of them.
 constexpr int kPanelQueueLog = 3;
-__host__ __device__ inline int panel_queue_log_tiles(int logM) {
-  return logM - 6 < kPanelQueueLog ? logM - 6 : kPanelQueueLog;
+constexpr int64_t kPanelQueueUnits = 1024;
+inline int panel_queue_log_tiles(int64_t tiles) {
+  int lt = 0;
+  while (lt < kPanelQueueLog && tiles >> (lt + 1) >= kPanelQueueUnits) ++lt;
+  return lt;
 }
 // Row kernel (k_rows.hip): the columns per lane (4, 2 or 1) with which a step
 // runs on it, or 0.  FP32 steps of at most two shared cuts, output not in

@@ -149,3 +149,23 @@ def test_outputs_and_targets_at_4_byte_alignment(f, k):
     assert torch.equal(batch.grads[0], cqc.xent_grad(p, t)) and torch.equal(batch.grads[0], batch.grads[1])
     for b in (bo, bg):
         assert float(b[0]) == 7.0 and float(b[-1]) == 7.0
+
+
+@pytest.mark.parametrize("f,count", [((10, 10), 2), ((11, 11), 2), ((11, 12), 2), ((12, 12), 2), ((13, 12), 1)])
+def test_panel_batch_runs(f, count):
+    """Batches whose units take one, two, four and eight row tiles (the launch's
+    tile count decides), next to an instance with a single row tile: the single
+    call's outputs bit for bit where that runs panels too, and the oracle's."""
+    _gpu()
+    shapes = [f] * count + [(6, 13)]
+    cuts_w = [W.CutMap(sum(s), list(s), [0] * 3, [1] * 3, list(range(sum(s)))) for s in shapes]
+    hosts, dev = zip(*[to_dev(_entries(c, 990 + i, 60), torch.float32) for i, c in enumerate(cuts_w)])
+    cuts = [cqc.CutMap.from_workload(c) for c in cuts_w]
+    batch = cqc.Batch(list(dev), cuts, precision="fp32")
+    batch.run()
+    for i, c in enumerate(cuts):
+        _check(cuts_w[i], batch.outs[i], hosts[i], 995 + i)
+        s, sa = float(batch.outs[i].double().sum()), float(batch.outs[i].double().abs().sum())
+        assert abs(float(batch.mass[i]) - s) <= 1e-12 * sa, i
+        if c.n >= 22:
+            assert torch.equal(batch.outs[i], cqc.reconstruct_fd(dev[i], c, precision="fp32")[0]), i
