@@ -216,16 +216,17 @@ Status run_net(const NetLayout &L, char *ws, const std::vector<const void *> &en
     if (cfg == kTileW && is_split(sa) && L.xs_off[i] != SIZE_MAX && !gate) {
       // split both operands into their bfloat16 parts once, for every tile
       const TensorSpec &X = p.tensors[st.x], &Y = p.tensors[st.y];
-      a.xplane = X.rows() * X.cols();
-      a.yplane = Y.rows() * Y.cols();
+      const int64_t xplane = X.rows() * X.cols(), yplane = Y.rows() * Y.cols();
+      a.xlog = 2 * (a.nS + a.nRX) + a.logM;
+      a.ylog = 2 * (a.nS + a.nRY) + a.logN;
       a.Xs = ws + L.xs_off[i];
       a.Ys = ws + L.ys_off[i];
       if (!in_parts[st.x])
-        CQC_TRY(launch_presplit(split_parts(sa), static_cast<const float *>(a.X), ws + L.xs_off[i], a.xplane,
-                                a.xplane, s));
+        CQC_TRY(launch_presplit(split_parts(sa), static_cast<const float *>(a.X), ws + L.xs_off[i], xplane,
+                                xplane, s));
       if (!in_parts[st.y])
-        CQC_TRY(launch_presplit(split_parts(sa), static_cast<const float *>(a.Y), ws + L.ys_off[i], a.yplane,
-                                a.yplane, s));
+        CQC_TRY(launch_presplit(split_parts(sa), static_cast<const float *>(a.Y), ws + L.ys_off[i], yplane,
+                                yplane, s));
     }
     if (!last && a.Xs) {
       // a result that only a split step of this run reads goes straight into
@@ -235,9 +236,7 @@ Status run_net(const NetLayout &L, char *ws, const std::vector<const void *> &en
         const Step &sj = p.steps[j];
         if (sj.x != st.z && sj.y != st.z) continue;
         if ((skip_final && j + 1 == p.steps.size()) || L.xs_off[j] == SIZE_MAX) break;
-        const TensorSpec &Z = p.tensors[st.z];
         a.Zs = ws + (sj.x == st.z ? L.xs_off[j] : L.ys_off[j]);
-        a.zplane = Z.rows() * Z.cols();
         in_parts[st.z] = 1;
         break;
       }

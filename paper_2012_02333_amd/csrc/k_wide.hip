@@ -305,7 +305,7 @@ __device__ __forceinline__ void wide_run(Seq &seq) {
       // part p of the two columns: 4 bytes at plane p, row offset / 2 (the
       // list holds FP32 byte offsets)
       const char *pb = reinterpret_cast<const char *>(roleX ? uni(a.Xs) : uni(a.Ys));
-      const int64_t plane2 = 2 * (roleX ? uni(a.xplane) : uni(a.yplane));
+      const int64_t plane2 = int64_t(2) << (roleX ? uni(a.xlog) : uni(a.ylog));
       const uint32_t col2 = colok[b][1] ? (uint32_t)colv * 2u : 0u;
 #pragma unroll
       for (int k = 0; k < kH; ++k)
@@ -484,7 +484,7 @@ __device__ __forceinline__ void wide_run(Seq &seq) {
     const bool parts = NP > 0 && MODE == kModeIntermediate && uni(a.Zs) != nullptr;
     auto put_parts = [&](int64_t o, const float (&w)[4], int count) {
       const gptr<__bf16> zs = gbl(uni(static_cast<__bf16 *>(a.Zs))) + g.batch * M * N + o;
-      const int64_t plane = uni(a.zplane);
+      const int64_t plane = uni(a.nbatch) * M * N;
       typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
       bf16x4 part[3];
 #pragma unroll

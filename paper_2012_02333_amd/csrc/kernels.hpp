@@ -65,34 +65,26 @@ struct ContractArgs {
   int32_t gate_val;
   int32_t panel;     // > 0: a wide step that runs on the panel kernel (every step of a queue group
                      //   alike); in a queue launch 1 + log2 of the row tiles of a unit
-  // A batch keeps one of these per step in the caller's workspace, whose size
-  // its users may have on record: what only single calls use and what only
-  // batches use share their place.
-  union {
-    struct {
-      // split-BF16 wide steps: the operands already split into bfloat16 parts,
-      // part p of X at Xs + p * xplane elements (same layout as X), or null (the
-      // wide kernel splits while staging)
-      const void *Xs;
-      const void *Ys;
-      int64_t xplane, yplane;
-      // split-BF16 intermediate steps whose result only a split step reads: the
-      // parts of Z are written here (part p at Zs + p * zplane elements) instead of Z
-      void *Zs;
-      int64_t zplane;
-    };
-    struct {
-      // cross-entropy form of a final step (batched launches): xt is the target
-      // t in output order; every output p gets dL/dp = -t/p (0 where p <= 1e-30)
-      // written to xg at its position, p itself is written only if Z is set, and
-      // the partial sums add the loss terms -t log max(p, 1e-30) (kernel form
-      // with the loss) or p
-      const void *xt;
-      void *xg;
-    };
-  };
+  // split-BF16 wide steps of single calls: the operands already split into
+  // bfloat16 parts, each part a plane of the operand's layout and size (2^xlog
+  // and 2^ylog elements), or null (the wide kernel splits while staging)
+  const void *Xs;
+  const void *Ys;
+  int32_t xlog, ylog;
+  // split-BF16 intermediate steps whose result only a split step reads: the
+  // parts of Z are written here, planes as above, instead of Z
+  void *Zs;
+  // cross-entropy form of a final step (batched launches): xt is the target t
+  // in output order; every output p gets dL/dp = -t/p (0 where p <= 1e-30)
+  // written to xg at its position, p itself is written only if Z is set, and
+  // the partial sums add the loss terms -t log max(p, 1e-30) (kernel form with
+  // the loss) or p
+  const void *xt;
+  void *xg;
 };
-static_assert(sizeof(ContractArgs) == 344, "the tables of a batch grow with it");
+// A batch keeps one of these per step in the caller's workspace, whose size its
+// users may have on record.
+static_assert(sizeof(ContractArgs) <= 344, "the workspaces of batches grow");
 
 // FP64 mass partials: every wave of a final-step tile (four per block) stores
 // the FP64 sum of the outputs it wrote at partials[kPartialsPerTile * tile +
