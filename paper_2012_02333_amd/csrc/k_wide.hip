@@ -520,7 +520,7 @@ __device__ __forceinline__ void wide_run(Seq &seq) {
         if constexpr (XE) {
           for (int r = 0; r < 4; ++r)
             if (n + r < N)
-              msum += xent_put1<O>(a, MODE == kModeFinalBlocked ? m * N + n + r
+              msum += xent_put1<O, true>(a, MODE == kModeFinalBlocked ? m * N + n + r
                                                                : rowoff[m - g.m0] + coloff[n + r - g.n0],
                                    v[r], XE == 2);
         } else {

@@ -162,13 +162,28 @@ __device__ __forceinline__ double xent_total(double sum) {
 }
 
 // One output p of a cross-entropy final step at element o of the output order:
-// gradient to xg, p to z if set; returns the partial-sum contribution.
-template <typename T>
+// gradient to xg, p to z if set; returns the partial-sum contribution.  GLB:
+// global accesses and the division of xent_grad_of.  The register kernels take
+// generic accesses and a conditional division where they write outputs one by
+// one (FP64, deposit order): they are bound by these scattered accesses, and
+// with the other form a wave has more of them under way at a time, which is
+// slower.  Sixteen FP32 instances of 18 qubits in deposit order take 128 us per
+// run, 166 with GLB; in FP64, blocked, 139 against 167.  The deposits of the
+// wide kernels are faster with it (sixteen of 19 qubits, BF16X6: 104 us against
+// 114).
+template <typename T, bool GLB = false>
 __device__ __forceinline__ double xent_put1(const ContractArgs &a, int64_t o, T p, bool loss) {
-  const T t = gbl(static_cast<const T *>(a.xt))[o];
-  if (a.Z) gbl(static_cast<T *>(a.Z))[o] = p;
-  gbl(static_cast<T *>(a.xg))[o] = xent_grad_of(p, t);
-  return xent_part(p, t, loss);
+  if constexpr (GLB) {
+    const T t = gbl(static_cast<const T *>(a.xt))[o];
+    if (a.Z) gbl(static_cast<T *>(a.Z))[o] = p;
+    gbl(static_cast<T *>(a.xg))[o] = xent_grad_of(p, t);
+    return xent_part(p, t, loss);
+  } else {
+    const T t = static_cast<const T *>(a.xt)[o];
+    if (a.Z) static_cast<T *>(a.Z)[o] = p;
+    static_cast<T *>(a.xg)[o] = xent_above(p) ? -t / p : T(0);
+    return xent_part(p, t, loss);
+  }
 }
 
 // Four consecutive outputs at elements o..o+3 (o a multiple of 4): vector
