@@ -358,22 +358,50 @@ __device__ __forceinline__ void contract_small_tile(const ContractArgs &a, uint3
     rrq[q] = sq < nSv ? make_int2(row_of(a.mx, sq, rX), row_of(a.my, sq, rY)) : make_int2(-1, -1);
   }
   T ay[4][BNB], bxa[BMB][4];
+  // Masked loads, or (`every`) unconditional ones as in contract_tile (column 0
+  // where the tile overhangs, row 0 for a missing term) whose missing terms are
+  // zeroed afterwards.  Unconditional: on the smaller tiles in FP32 or with all
+  // 16 terms (2^18 x 2^6 FP64 outputs 53 us, masked 56), for FP64 outputs of the
+  // 64 x 256 tile in deposit order (2^13 x 2^11: 144, masked 155) and in the
+  // cross-entropy form.  Elsewhere they cost registers, load rows in place of
+  // missing terms and crowd scattered stores: 2^18 x 2^6 FP64 outputs of one
+  // term 39.5 us, masked 36.2; on the 64 x 256 tile 2^11 x 2^13 FP32 outputs of
+  // FP64 entries 23.3 and 20.3, 2^13 x 2^11 in deposit order 84.5 and 69.5.
+  const bool every = XE != 0 || (BMB * BNB <= 4 ? sizeof(T) == 4 || nSv == 16 : MODE == kModeFinalDeposit && sizeof(O) == 8);
   auto load_ops = [&]() {
+    if (every) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool kok = rrq[q].x >= 0;
+        const gptr<const T> yr = gbl(Y) + (int64_t)(kok ? rrq[q].y : 0) * N;
+        const gptr<const T> xr = gbl(X) + (int64_t)(kok ? rrq[q].x : 0) * M;
+#pragma unroll
+        for (int j = 0; j < BNB; ++j) {
+          const int64_t c = nw + j * 16 + l16;
+          ay[q][j] = yr[c < N ? c : 0];
+        }
+#pragma unroll
+        for (int i = 0; i < BMB; ++i) {
+          const int64_t c = mw + i * 16 + l16;
+          bxa[i][q] = xr[c < M ? c : 0];
+        }
+      }
+      return;
+    }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const bool kok = rrq[q].x >= 0;
-      const gptr<const T> yr = gbl(Y) + (int64_t)(kok ? rrq[q].y : 0) * N;
-      const gptr<const T> xr = gbl(X) + (int64_t)(kok ? rrq[q].x : 0) * M;
-      // unconditional loads (column 0 where the tile overhangs), as in contract_tile
+      const T *yr = Y + (int64_t)(kok ? rrq[q].y : 0) * N;
+      const T *xr = X + (int64_t)(kok ? rrq[q].x : 0) * M;
 #pragma unroll
       for (int j = 0; j < BNB; ++j) {
         const int64_t c = nw + j * 16 + l16;
-        ay[q][j] = yr[c < N ? c : 0];
+        ay[q][j] = (kok && c < N) ? yr[c] : (T)0;
       }
 #pragma unroll
       for (int i = 0; i < BMB; ++i) {
         const int64_t c = mw + i * 16 + l16;
-        bxa[i][q] = xr[c < M ? c : 0];
+        bxa[i][q] = (kok && c < M) ? xr[c] : (T)0;
       }
     }
   };
@@ -411,7 +439,7 @@ __device__ __forceinline__ void contract_small_tile(const ContractArgs &a, uint3
     for (int q = 0; q < 4; ++q) rrq[q] = lst[4 * q + lg];
     load_ops();
   }
-  if (cnt_sh < 16) zero_missing();
+  if (every && cnt_sh < 16) zero_missing();
 
   double msum = 0.0;
   const O scale = (O)a.scale;
