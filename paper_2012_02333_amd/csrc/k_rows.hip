@@ -20,16 +20,14 @@
 // replaces: 389 M outputs of the cross-entropy form 785 us there, 582 here (8
 // bytes each: 5.3 TB/s); 2^30 outputs of 16 terms 787 and 755 us; 2^24 outputs
 // of 16 terms 15.5 and 14.8 us; 42 M outputs 128 columns wide, cross-entropy
-// form, 149 us on 32 x 128 tiles and 64 here.
+// form, 149 us on 32 x 128 tiles and 64 here.  (Trace names with "strip" are those
+// of the step class: users of the trace know it by the kernel that ran it before.)
 #include <algorithm>
 #include <type_traits>
 
 #include "kdev.hpp"
 
 namespace cqc {
-
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 // The C columns of a lane: C consecutive ones, or for FP64 outputs two pairs
 // 128 columns apart (16 bytes each), so every access of a wave is contiguous.
@@ -38,10 +36,12 @@ template <typename O, int C> struct RowCols {
   static __device__ __forceinline__ uint32_t col(int lane) { return (uint32_t)((kPairs ? 2 : C) * lane); }
 };
 
+// Rows may be aligned to an element only.
+typedef float u2 __attribute__((ext_vector_type(2), aligned(4)));
+typedef float u4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+
 template <int C> __device__ __forceinline__ void load_cols(gptr<const char> p, bool pairs, float (&v)[C]) {
-  // rows may be 4-byte aligned only
-  typedef float u2 __attribute__((ext_vector_type(2), aligned(4)));
-  typedef float u4 __attribute__((ext_vector_type(4), aligned(4)));
   if constexpr (C == 4) {
     if (pairs) {
       const u2 a = *(gptr<const u2>)p, b = *(gptr<const u2>)(p + 512);
@@ -59,28 +59,36 @@ template <int C> __device__ __forceinline__ void load_cols(gptr<const char> p, b
   }
 }
 
-// Outputs are written once and not read here: non-temporal.
-template <int C> __device__ __forceinline__ void store_cols(gptr<char> p, const float (&v)[C]) {
-  typedef float u2 __attribute__((ext_vector_type(2), aligned(4)));
-  typedef float u4 __attribute__((ext_vector_type(4), aligned(4)));
-  if constexpr (C == 4) __builtin_nontemporal_store(u4{v[0], v[1], v[2], v[3]}, (gptr<u4>)p);
-  else if constexpr (C == 2) __builtin_nontemporal_store(u2{v[0], v[1]}, (gptr<u2>)p);
-  else __builtin_nontemporal_store(v[0], (gptr<float>)p);
+// Outputs are written once and not read here: non-temporal.  PLAIN (the next
+// step reads them, or rows_plain_stores): ordinary stores.
+template <bool PLAIN> __device__ __forceinline__ void store_d2(gptr<char> p, double a, double b) {
+  if constexpr (PLAIN) *(gptr<d2>)p = d2{a, b};
+  else __builtin_nontemporal_store(d2{a, b}, (gptr<d2>)p);
 }
-template <int C> __device__ __forceinline__ void store_cols(gptr<char> p, const double (&v)[C]) {
-  typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+template <bool PLAIN, int C> __device__ __forceinline__ void store_cols(gptr<char> p, const float (&v)[C]) {
   if constexpr (C == 4) {
-    __builtin_nontemporal_store(d2{v[0], v[1]}, (gptr<d2>)p);
-    __builtin_nontemporal_store(d2{v[2], v[3]}, (gptr<d2>)(p + 1024));
+    if constexpr (PLAIN) *(gptr<u4>)p = u4{v[0], v[1], v[2], v[3]};
+    else __builtin_nontemporal_store(u4{v[0], v[1], v[2], v[3]}, (gptr<u4>)p);
   } else if constexpr (C == 2) {
-    __builtin_nontemporal_store(d2{v[0], v[1]}, (gptr<d2>)p);
+    if constexpr (PLAIN) *(gptr<u2>)p = u2{v[0], v[1]};
+    else __builtin_nontemporal_store(u2{v[0], v[1]}, (gptr<u2>)p);
   } else {
-    __builtin_nontemporal_store(v[0], (gptr<double>)p);
+    if constexpr (PLAIN) *(gptr<float>)p = v[0];
+    else __builtin_nontemporal_store(v[0], (gptr<float>)p);
+  }
+}
+template <bool PLAIN, int C> __device__ __forceinline__ void store_cols(gptr<char> p, const double (&v)[C]) {
+  if constexpr (C == 4) {
+    store_d2<PLAIN>(p, v[0], v[1]);
+    store_d2<PLAIN>(p + 1024, v[2], v[3]);
+  } else if constexpr (C == 2) {
+    store_d2<PLAIN>(p, v[0], v[1]);
+  } else {
+    if constexpr (PLAIN) *(gptr<double>)p = v[0];
+    else __builtin_nontemporal_store(v[0], (gptr<double>)p);
   }
 }
 template <int C> __device__ __forceinline__ void load_targets(gptr<const char> p, float (&v)[C]) {
-  typedef float u2 __attribute__((ext_vector_type(2), aligned(4)));
-  typedef float u4 __attribute__((ext_vector_type(4), aligned(4)));
   if constexpr (C == 4) {
     const u4 a = __builtin_nontemporal_load((gptr<const u4>)p);
 #pragma unroll
@@ -94,8 +102,8 @@ template <int C> __device__ __forceinline__ void load_targets(gptr<const char> p
 }
 
 // One unit (this wave): columns n0 .. n0 + 64 C - 1 of 2^lt 16-row tiles.
-// KEEP: p is written too in the cross-entropy form.
-template <typename O, int MODE, int XE, bool KEEP, int C, int NS>
+// KEEP: p is written too in the cross-entropy form.  PLAIN: ordinary stores.
+template <typename O, int MODE, int XE, bool KEEP, int C, int NS, bool PLAIN = false>
 __device__ __forceinline__ void rows_unit(const ContractArgs &a, int lt, int64_t unit) {
   constexpr int K = 1 << (2 * NS), NV = K >= 4 ? K / 4 : 1;
   constexpr int kLogC = C == 4 ? 2 : C == 2 ? 1 : 0;
@@ -229,17 +237,17 @@ __device__ __forceinline__ void rows_unit(const ContractArgs &a, int lt, int64_t
             msum += xent_part(v[c], t, XE == 2);
           }
           if constexpr (KEEP) {
-            store_cols<C>(Zr + zc, v);
+            store_cols<false, C>(Zr + zc, v);
             advance(Zr);
           }
-          store_cols<C>(Gr + zc, gr);
+          store_cols<false, C>(Gr + zc, gr);
           advance(Gr);
           // one row's arithmetic in registers at a time (the sum would be put
           // off, with all its operands alive)
           asm volatile("" : "+v"(msum));
           __builtin_amdgcn_sched_barrier(0);
         } else {
-          store_cols<C>(Zr + zc, v);
+          store_cols<PLAIN, C>(Zr + zc, v);
           advance(Zr);
           if (MODE != kModeIntermediate) {
             if constexpr (C == 4) msum += ((double)v[0] + (double)v[1]) + ((double)v[2] + (double)v[3]);
@@ -263,10 +271,10 @@ __device__ __forceinline__ void rows_unit(const ContractArgs &a, int lt, int64_t
   }
 }
 
-template <typename O, int MODE, int C, int NS>
+template <typename O, int MODE, int C, int NS, bool PLAIN>
 __global__ __launch_bounds__(256) void k_rows(const ContractArgs a, int lt) {
   if (gated_off(a.gate, a.gate_val)) return;
-  rows_unit<O, MODE, 0, true, C, NS>(a, lt, (int64_t)blockIdx.x * 4 + uni((int32_t)(threadIdx.x >> 6)));
+  rows_unit<O, MODE, 0, true, C, NS, PLAIN>(a, lt, (int64_t)blockIdx.x * 4 + uni((int32_t)(threadIdx.x >> 6)));
 }
 
 // Many steps of one shape class per launch: block b belongs to the step d with
@@ -279,7 +287,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NS == 2 ? 3
   const ContractArgs &a = descs[d];
   const int lt = rows_log_tiles(uni(a.logM), uni(a.logN), 2 * (uni(a.nRX) + uni(a.nRY)), C, NS);
   const int64_t unit = ((int64_t)blockIdx.x - uni(prefix[d])) * 4 + uni((int32_t)(threadIdx.x >> 6));
-  if (XE == 0 || uni(a.Z)) rows_unit<float, MODE, XE, true, C, NS>(a, lt, unit);
+  if (XE == 0 || uni(a.Z)) rows_unit<float, MODE, XE, true, C, NS, MODE == kModeIntermediate>(a, lt, unit);
   else rows_unit<float, MODE, XE, XE == 0, C, NS>(a, lt, unit);
 }
 
@@ -288,19 +296,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NS == 2 ? 3
 // kernel, so the same bits.  The even and odd columns of 32 sit in two products:
 // a lane's pair of accumulators is 16 adjacent bytes, and one instruction
 // writes 256 contiguous bytes of four rows (128 from the register kernel, which
-// also loads Y again for every 64 rows).  2^25 outputs of 16 terms: 55 us there
-// (4.9 TB/s), 49 here (46 with ordinary stores, but the calls of a loop then
-// take 70.0 instead of 67.1 us: the write-back falls to the next kernel); a fill of that size takes 39.
-template <int MODE, int NS>
-__device__ __forceinline__ void rows64_unit(const ContractArgs &a, int lt, int64_t unit) {
+// also loads Y again for every 64 rows).  One row tile per wave: 2^9 x 2^16 outputs
+// of 16 terms took 48.8, 54.5, 55.5, 55.5 us with 1, 2, 4, 8.  2^10 x 2^12 outputs
+// take 0.86 of the register kernel's time, 2^9 x 2^15 0.95, 2^9 x 2^16 0.97 (one,
+// four and 16 terms alike).
+template <int MODE, int NS, bool PLAIN>
+__device__ __forceinline__ void rows64_unit(const ContractArgs &a, int64_t unit) {
   constexpr int K = 1 << (2 * NS), NQ = K >= 4 ? K / 4 : 1, NB = 8;
   const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
   const int logM = uni(a.logM), logN = uni(a.logN);
-  const int lp = logN - 7, lr = logM - 4 - lt;
+  const int lp = logN - 7, lr = logM - 4;
   const int64_t batch = unit >> (lp + lr);
   if (batch >= a.nbatch) return;
   const int64_t n0 = (unit & ((int64_t(1) << lp) - 1)) << 7;
-  const int64_t m0 = ((unit >> lp) & ((int64_t(1) << lr) - 1)) << (4 + lt);
+  const int64_t m0 = ((unit >> lp) & ((int64_t(1) << lr) - 1)) << 4;
   const int rX = (int)(batch >> (2 * a.nRY)), rY = (int)(batch & ((int64_t(1) << (2 * a.nRY)) - 1));
   // rows of the operands: lane t < K computes those of term t, and whether it is live
   const int rx = lane < K ? row_of(a.mx, lane, rX) : 0, ry = lane < K ? row_of(a.my, lane, rY) : 0;
@@ -308,9 +317,7 @@ __device__ __forceinline__ void rows64_unit(const ContractArgs &a, int lt, int64
   if (uni(a.flagX) != nullptr)
     live = (uint32_t)__ballot(lane < K && (row_live(a.flagX, a.nchX, rx) & row_live(a.flagY, a.nchY, ry)));
   const gptr<const double> Xb = gbl(static_cast<const double *>(uni(a.X))), Yb = gbl(static_cast<const double *>(uni(a.Y)));
-  typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
   double y[NQ][NB], x[NQ];
-  gptr<const double> xp[NQ];
   bool ok[NQ];   // this lane's term of the quad is live
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
@@ -323,42 +330,32 @@ __device__ __forceinline__ void rows64_unit(const ContractArgs &a, int lt, int64
       y[q][2 * p] = v[0];
       y[q][2 * p + 1] = v[1];
     }
-    xp[q] = Xb + ((int64_t)__shfl(rx, ts, 64) << logM) + m0 + l16;
-    x[q] = *xp[q];
+    x[q] = Xb[((int64_t)__shfl(rx, ts, 64) << logM) + m0 + l16];
   }
 #pragma unroll
-  for (int q = 0; q < NQ; ++q)
+  for (int q = 0; q < NQ; ++q) {
+    x[q] = ok[q] ? x[q] : 0.0;
 #pragma unroll
     for (int j = 0; j < NB; ++j) y[q][j] = ok[q] ? y[q][j] : 0.0;
+  }
   const double sc = MODE == kModeIntermediate ? 1.0 : uni(a.scale);
   gptr<double> Z = gbl(static_cast<double *>(uni(a.Z))) + (MODE == kModeIntermediate ? batch << (logM + logN) : 0) +
                    ((m0 + lg) << logN) + n0 + 2 * l16;
   double msum = 0.0;
-  const int tiles = 1 << lt;
-  for (int it = 0; it < tiles; ++it) {
-    double xv[NQ];
+#pragma unroll
+  for (int p = 0; p < NB / 2; ++p) {
+    f64x4 e{0, 0, 0, 0}, o{0, 0, 0, 0};
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-      xv[q] = ok[q] ? x[q] : 0.0;
-      if (it + 1 < tiles) xp[q] += 16;   // the last tile reloads itself
-      x[q] = *xp[q];
+      e = MfmaOp<double>::run(x[q], y[q][2 * p], e);
+      o = MfmaOp<double>::run(x[q], y[q][2 * p + 1], o);
     }
 #pragma unroll
-    for (int p = 0; p < NB / 2; ++p) {
-      f64x4 e{0, 0, 0, 0}, o{0, 0, 0, 0};
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        e = MfmaOp<double>::run(xv[q], y[q][2 * p], e);
-        o = MfmaOp<double>::run(xv[q], y[q][2 * p + 1], o);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const d2 v = {e[r] * sc, o[r] * sc};
-        __builtin_nontemporal_store(v, (gptr<d2>)(Z + ((int64_t)(4 * r) << logN) + 32 * p));
-        if (MODE != kModeIntermediate) msum += v[0] + v[1];
-      }
+    for (int r = 0; r < 4; ++r) {
+      const double v0 = e[r] * sc, v1 = o[r] * sc;
+      store_d2<PLAIN>((gptr<char>)(Z + ((int64_t)(4 * r) << logN) + 32 * p), v0, v1);
+      if (MODE != kModeIntermediate) msum += v0 + v1;
     }
-    Z += int64_t(16) << logN;
   }
   if (MODE == kModeIntermediate) {
     if (a.flagZ && lane == 0 && (unit & ((int64_t(1) << (lp + lr)) - 1)) == 0) gbl(a.flagZ)[batch] = live != 0;
@@ -368,10 +365,10 @@ __device__ __forceinline__ void rows64_unit(const ContractArgs &a, int lt, int64
   }
 }
 
-template <int MODE, int NS>
-__global__ __launch_bounds__(256) void k_rows_f64(const ContractArgs a, int lt) {
+template <int MODE, int NS, bool PLAIN>
+__global__ __launch_bounds__(256) void k_rows_f64(const ContractArgs a) {
   if (gated_off(a.gate, a.gate_val)) return;
-  rows64_unit<MODE, NS>(a, lt, (int64_t)blockIdx.x * 4 + uni((int32_t)(threadIdx.x >> 6)));
+  rows64_unit<MODE, NS, PLAIN>(a, (int64_t)blockIdx.x * 4 + uni((int32_t)(threadIdx.x >> 6)));
 }
 
 int64_t rows_units(const ContractArgs &a) {
@@ -379,19 +376,24 @@ int64_t rows_units(const ContractArgs &a) {
   return a.nbatch << (a.logM - 4 - lt + a.logN - 6 - (a.rows == 4 ? 2 : a.rows == 2 ? 1 : 0));
 }
 
-// One tile per wave: 2^9 x 2^16 outputs of 16 terms took 48.8, 54.5, 55.5, 55.5
-// us with 1, 2, 4, 8 tiles.
 int64_t rows_f64_units(const ContractArgs &a) { return a.nbatch << (a.logM - 4 + a.logN - 7); }
 
-template <typename O, int MODE, int C>
-static Status launch_rows_c(const char *nm, const ContractArgs &a, hipStream_t s) {
+template <typename O, int MODE, int C, bool PLAIN>
+static Status launch_rows_p(const char *nm, const ContractArgs &a, hipStream_t s) {
   const int lt = rows_log_tiles(a.logM, a.logN, 2 * (a.nRX + a.nRY), a.rows, a.nS);
   const dim3 grid((unsigned)((rows_units(a) + 3) / 4)), block(256);
   switch (a.nS) {
-    case 0: return launch(nm, k_rows<O, MODE, C, 0>, grid, block, 0, s, a, lt);
-    case 1: return launch(nm, k_rows<O, MODE, C, 1>, grid, block, 0, s, a, lt);
-    default: return launch(nm, k_rows<O, MODE, C, 2>, grid, block, 0, s, a, lt);
+    case 0: return launch(nm, k_rows<O, MODE, C, 0, PLAIN>, grid, block, 0, s, a, lt);
+    case 1: return launch(nm, k_rows<O, MODE, C, 1, PLAIN>, grid, block, 0, s, a, lt);
+    default: return launch(nm, k_rows<O, MODE, C, 2, PLAIN>, grid, block, 0, s, a, lt);
   }
+}
+
+template <typename O, int MODE, int C>
+static Status launch_rows_c(const char *nm, const ContractArgs &a, hipStream_t s) {
+  if (MODE == kModeIntermediate || rows_plain_stores(a.nS, a.logM, a.logN, false, sizeof(O) == 8))
+    return launch_rows_p<O, MODE, C, true>(nm, a, s);
+  return launch_rows_p<O, MODE, C, MODE == kModeIntermediate>(nm, a, s);
 }
 
 template <typename O, int MODE>
@@ -411,22 +413,23 @@ Status launch_rows(bool out_double, const ContractArgs &a, hipStream_t s) {
   return out_double ? launch_rows_m<double, kModeFinalBlocked>(a, s) : launch_rows_m<float, kModeFinalBlocked>(a, s);
 }
 
-template <int MODE>
+template <int MODE, bool PLAIN>
 static Status launch_rows_f64_m(const ContractArgs &a, hipStream_t s) {
-  const int lt = 0;
   const dim3 grid((unsigned)((rows_f64_units(a) + 3) / 4)), block(256);
-  const char *nm = "contract_small_64x256";   // the register kernel's name: its FP64 form
+  const char *nm = MODE == kModeIntermediate ? "contract_rows_f64_inter" : "contract_rows_f64";
   switch (a.nS) {
-    case 0: return launch(nm, k_rows_f64<MODE, 0>, grid, block, 0, s, a, lt);
-    case 1: return launch(nm, k_rows_f64<MODE, 1>, grid, block, 0, s, a, lt);
-    default: return launch(nm, k_rows_f64<MODE, 2>, grid, block, 0, s, a, lt);
+    case 0: return launch(nm, k_rows_f64<MODE, 0, PLAIN>, grid, block, 0, s, a);
+    case 1: return launch(nm, k_rows_f64<MODE, 1, PLAIN>, grid, block, 0, s, a);
+    default: return launch(nm, k_rows_f64<MODE, 2, PLAIN>, grid, block, 0, s, a);
   }
 }
 
 Status launch_rows_f64(const ContractArgs &a, hipStream_t s) {
   if (a.rows != 2 || a.nS > 2 || a.logM < 4 || a.logN < 7 || a.mode == kModeFinalDeposit)
     return Status::fail(CQC_ERR_INVALID_ARG, "row contraction: step shape");
-  return a.mode == kModeIntermediate ? launch_rows_f64_m<kModeIntermediate>(a, s) : launch_rows_f64_m<kModeFinalBlocked>(a, s);
+  if (a.mode == kModeIntermediate) return launch_rows_f64_m<kModeIntermediate, true>(a, s);
+  return rows_plain_stores(a.nS, a.logM, a.logN, true, true) ? launch_rows_f64_m<kModeFinalBlocked, true>(a, s)
+                                                             : launch_rows_f64_m<kModeFinalBlocked, false>(a, s);
 }
 
 template <int MODE, int XE, int C>
@@ -441,14 +444,16 @@ static Status launch_rows_table_c(const char *nm, int nS, const QueueLaunch &q, 
 
 template <int MODE, int XE>
 static Status launch_rows_table_m(int rows, int nS, const QueueLaunch &q, hipStream_t s) {
-  const bool wide = rows == 4;
-  const char *nm = XE == 2 ? (wide ? "contract_strip_queue_xent_loss" : "contract_small_queue_xent_loss")
-                   : XE    ? (wide ? "contract_strip_queue_xent" : "contract_small_queue_xent")
-                           : (wide ? "contract_strip_queue" : "contract_small_queue");
+  constexpr auto name = [](const char *plain, const char *grad, const char *loss) {
+    return XE == 2 ? loss : XE ? grad : plain;
+  };
   switch (rows) {
-    case 4: return launch_rows_table_c<MODE, XE, 4>(nm, nS, q, s);
-    case 2: return launch_rows_table_c<MODE, XE, 2>(nm, nS, q, s);
-    default: return launch_rows_table_c<MODE, XE, 1>(nm, nS, q, s);
+    case 4: return launch_rows_table_c<MODE, XE, 4>(
+        name("contract_strip_queue", "contract_rows_256_xent", "contract_rows_256_xent_loss"), nS, q, s);
+    case 2: return launch_rows_table_c<MODE, XE, 2>(
+        name("contract_rows_128", "contract_rows_128_xent", "contract_rows_128_xent_loss"), nS, q, s);
+    default: return launch_rows_table_c<MODE, XE, 1>(
+        name("contract_rows_64", "contract_rows_64_xent", "contract_rows_64_xent_loss"), nS, q, s);
   }
 }
 

@@ -248,25 +248,48 @@ inline int rows_cols(Acc acc, int mode, int cfg, int nS, int logM, int logN, int
     default: return 0;
   }
 }
-// The same for the FP64 form of a single call with FP64 output: 2 (128 columns) or 0.
+// The same for the FP64 form of a single call with FP64 output: 2 (128 columns)
+// or 0.  Tiles L and M only, which the tile rule gives a single call's step from
+// 2^20 outputs (256 blocks); below, 16 x 64 register tiles fill the chip better.
+// With 16 terms and rows of 2^18 columns or more, Y (32 MiB and up) no longer
+// stays in the caches from one row tile to the next: 2^6 x 2^18 outputs took 35.5
+// us here, 30 on the register kernel, which reads Y once per 64 rows (2^8 x 2^16:
+// 28.8 and 30.6).
 inline int rows_cols_f64(int mode, int cfg, int nS, int logM, int logN, int log_batch) {
   return (cfg == kTileL || cfg == kTileM) && mode != kModeFinalDeposit && nS <= 2 && logM >= 4 && logN >= 7 &&
-         logM + logN + log_batch >= kRowsMinLog ? 2 : 0;
+         logM + logN + log_batch >= kRowsMinLog && (nS < 2 || logN <= 17 || logM <= 5) ? 2 : 0;
 }
 // 16-row tiles per wave (log2).  Longer runs reload Y less often, but spread
-// the rows that the chip writes at one time over more memory: two tiles at 16
-// terms as long as that leaves 2048 waves (2^11 x 2^13 outputs: 17.0, 14.8,
-// 14.8, 23 us for 1, 2, 4, 8 tiles; 2^20 x 2^10: 890, 753, 765, 808), four with
-// fewer terms as long as that leaves 1024 (2^12 x 2^12: 14.4, 14.8, 12.7, 21).
-// Rows of 2^15 columns and more are long enough by themselves (2^11 x 2^15: 47.0,
-// 56.2, 58.4 us for 1, 2, 4 tiles of 4 terms; 56.3, 60.8, 62.7 of 16).
+// the rows that the chip writes at one time over more memory: at most two tiles
+// at 16 terms and four with fewer, as long as that leaves 2048 waves (1024 with
+// fewer terms) and a run covers at most 2^18 outputs of whole rows (16 2^lt rows;
+// 1 MiB in FP32: beyond that the runs of a panel get slower).  One and four terms,
+// us for 1, 2 and 4 tiles: 2^12 x 2^14 outputs 50, 55, 66; 2^13 x 2^13 52, 48, 55;
+// 2^14 x 2^12 57, 55, 49; 2^13 x 2^14 95, 113, 129; 2^14 x 2^14 185, 219, 249.  16
+// terms, 1 and 2 tiles: 2^13 x 2^14 103, 113; 2^14 x 2^14 202, 216; 2^20 x 2^10 890,
+// 753 (four: 765).
 __host__ __device__ inline int rows_log_tiles(int logM, int logN, int log_batch, int rows, int nS) {
   const int waves = logM - 4 + logN - 6 - (rows == 4 ? 2 : rows == 2 ? 1 : 0) + log_batch;
   const int most = nS == 2 ? 1 : 2;
   int lt = waves - (nS == 2 ? 11 : 10);
   if (lt > most) lt = most;
   if (lt > logM - 4) lt = logM - 4;
-  return lt < 0 || logN >= 15 ? 0 : lt;
+  if (lt > 14 - logN) lt = 14 - logN;
+  return lt < 0 ? 0 : lt;
+}
+// Whether a single call's final row kernel writes with ordinary stores.
+// Outputs of 64 to 256 MiB stay in the 256 MiB last-level cache, so that the
+// write-back overlaps what follows: 2^12 x 2^14 FP32 outputs of one term 44 us,
+// 50 with non-temporal stores; 2^9 x 2^16 FP64 ones 46 and 54.  Smaller and larger
+// ones are faster with non-temporal stores (2^10 x 2^12: 8.2 and 8.7; 2^14 x 2^14: 185
+// and 189).  At 16 terms the operands need that cache as well: FP32 outputs from
+// 128 MiB (2^11 x 2^13 in a loop over circuits: 18.8 us, ordinary stores 19.5), rows
+// of at most 2^16 columns (2^7 x 2^18: 29 and 37 us), FP64 outputs of 256 MiB up to
+// 2^15 rows (2^15 x 2^10: 56 and 49; 2^16 x 2^9: 59 and 65).
+inline bool rows_plain_stores(int nS, int logM, int logN, bool f64, bool f64_out) {
+  const int log_bytes = logM + logN + (f64_out ? 3 : 2);
+  if (log_bytes < 26 || log_bytes > 28) return false;
+  return nS < 2 || (logN <= 16 && (f64_out || log_bytes > 26) && (!f64 || log_bytes < 28 || logM <= 15));
 }
 // Waves of a step: one FP64 partial each in a final step, four per block.
 int64_t rows_units(const ContractArgs &a);
