@@ -474,7 +474,8 @@ Status launch_panel_queue(int mode, const QueueLaunch &q, hipStream_t s) {
   if (!q.bprefix || q.btotal < 1) return Status::fail(CQC_ERR_INVALID_ARG, "panel queue without label-list table");
   const dim3 grid(q.grid), block(256);
   CQC_TRY(launch_label_list_table(q, s));
-  const char *nm = "wide_f32_queue", *nx = "wide_f32_queue_xent";
+  const char *nm = q.stream ? "wide_f32_queue_stream" : "wide_f32_queue";
+  const char *nx = q.stream ? "wide_f32_queue_xent_stream" : "wide_f32_queue_xent_panel";
   if (q.stream) {
     if (mode == kModeIntermediate)
       return launch(nm, k_stream_queue<kModeIntermediate, 0>, grid, block, 0, s, q.descs, q.prefix, q.ndesc, q.queue, q.total);
