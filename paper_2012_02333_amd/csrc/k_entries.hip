@@ -63,8 +63,11 @@ __device__ __forceinline__ void mode_products(double (&u)[1 << (2 * KIN)]) {
 // Subcircuits with one or two incoming cuts and no outgoing one, FP32 in and
 // out: four adjacent columns per thread.  Bound by its bytes, half read, half
 // written; with one column per thread (4 bytes per access) 2^22 columns of two
-// cuts took 172 us, 3.1 TB/s, with four 115 us.  The columns take turns in the
-// FP64 products, so only the 4 x 4^KIN floats stay in registers.
+// cuts took 146 us, with four 83 (125 when four sets of buffers take turns).  The
+// columns take turns in the FP64 products, so only the 4 x 4^KIN floats stay in
+// registers.  Ordinary loads: the variants may be in the caches, where they were
+// just written (2^21 columns: 45 us, non-temporal loads 58, one column per thread
+// 44).  FP64 keeps the general kernel, whose accesses are 8 bytes wide.
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 template <int KIN, int EIGEN>
@@ -76,7 +79,7 @@ __global__ __launch_bounds__(256) void k_build_entries_in(const EntryArgs a) {
   float *E = static_cast<float *>(a.E) + x;
   f32x4u v[NI];
 #pragma unroll
-  for (int i = 0; i < NI; ++i) v[i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4u *>(V + i * nx));
+  for (int i = 0; i < NI; ++i) v[i] = *reinterpret_cast<const f32x4u *>(V + i * nx);
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     double u[NI];
