@@ -10,7 +10,7 @@ namespace cqc {
 // 2^kMergeLogChunk combinations): lanes strided over the chunk with eight
 // accumulators each, combined in a fixed tree and a fixed butterfly; an
 // output with one chunk is written directly, otherwise its chunk sums go to
-// `part` and k_dd_merge_chunks adds them in chunk order.  With fewer merged
+// `part` and k_dd_merge_chunks adds them, in a fixed order.  With fewer merged
 // combinations one thread takes each output, in ascending m.
 template <typename I, typename O>
 __global__ __launch_bounds__(256) void k_dd_merge(const MergeArgs a) {

@@ -221,7 +221,9 @@ int cqc_autotune(const cqc_instance *inst, int32_t n_inst, cqc_dtype in_t, cqc_d
         ents[c] = inst[i].entries[c];
       }
     }
-    // one full run computes the flags and every intermediate
+    // one full run computes the flags and the intermediates (in split plans as
+    // bfloat16 parts where a split step reads them); the steps are then timed in
+    // order, and each writes the intermediate that the later ones read
     st = run_net(ip.net, ws, ents, inst[i].out, out_t == CQC_F64, nullptr, true, stream);
     if (!st.good()) return st.code;
     for (size_t s = 0; s < ip.net.plan.steps.size(); ++s) {
