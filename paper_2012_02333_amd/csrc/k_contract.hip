@@ -243,7 +243,7 @@ __device__ __forceinline__ void contract_tile(const ContractArgs &a, uint32_t bl
             } else {
               for (int r = 0; r < 4; ++r)
                 if (n + r < N)
-                  msum += xent_put1<O>(a, MODE == kModeFinalBlocked ? m * N + n + r
+                  msum += xent_put1<O, XE == 2 && sizeof(O) == 8>(a, MODE == kModeFinalBlocked ? m * N + n + r
                                                                    : rowoff[m - (int64_t)tm * BM] +
                                                                          coloff[n + r - (int64_t)tn * BN],
                                        v[r], XE == 2);
@@ -282,7 +282,7 @@ __device__ __forceinline__ void contract_tile(const ContractArgs &a, uint32_t bl
                                   ? m * N + n
                                   : rowoff[m - (int64_t)tm * BM] + coloff[n - (int64_t)tn * BN];
             if constexpr (XE) {
-              msum += xent_put1<O>(a, o, v, XE == 2);
+              msum += xent_put1<O, XE == 2 && sizeof(O) == 8>(a, o, v, XE == 2);
             } else {
               static_cast<O *>(a.Z)[o] = v;
               msum += (double)v;
@@ -523,7 +523,7 @@ __device__ __forceinline__ void contract_small_tile(const ContractArgs &a, uint3
             } else {
               for (int r = 0; r < 4; ++r)
                 if (n + r < N)
-                  msum += xent_put1<O>(a, MODE == kModeFinalBlocked ? m * N + n + r
+                  msum += xent_put1<O, XE == 2 && sizeof(O) == 8>(a, MODE == kModeFinalBlocked ? m * N + n + r
                                                                    : rowoff[m - (int64_t)tm * BM] +
                                                                          coloff[n + r - (int64_t)tn * BN],
                                        v[r], XE == 2);
@@ -559,7 +559,7 @@ __device__ __forceinline__ void contract_small_tile(const ContractArgs &a, uint3
                                   ? m * N + n
                                   : rowoff[m - (int64_t)tm * BM] + coloff[n - (int64_t)tn * BN];
             if constexpr (XE) {
-              msum += xent_put1<O>(a, o, v, XE == 2);
+              msum += xent_put1<O, XE == 2 && sizeof(O) == 8>(a, o, v, XE == 2);
             } else {
               static_cast<O *>(a.Z)[o] = v;
               msum += (double)v;

@@ -168,9 +168,10 @@ __device__ __forceinline__ double xent_total(double sum) {
 // one (FP64, deposit order): they are bound by these scattered accesses, and
 // with the other form a wave has more of them under way at a time, which is
 // slower.  Sixteen FP32 instances of 18 qubits in deposit order take 128 us per
-// run, 166 with GLB; in FP64, blocked, 139 against 167.  The deposits of the
-// wide kernels are faster with it (sixteen of 19 qubits, BF16X6: 104 us against
-// 114).
+// run, 166 with GLB; in FP64, blocked, 139 against 167.  Bound by arithmetic
+// instead, FP64 with the loss is faster with GLB (64 instances of 12 to 19 qubits
+// in deposit order: 551 us, 606 without), and so are the deposits of the wide kernels (sixteen
+// of 19 qubits, BF16X6: 104 us against 114).
 template <typename T, bool GLB = false>
 __device__ __forceinline__ double xent_put1(const ContractArgs &a, int64_t o, T p, bool loss) {
   if constexpr (GLB) {

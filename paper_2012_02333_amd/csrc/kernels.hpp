@@ -284,12 +284,13 @@ __host__ __device__ inline int rows_log_tiles(int logM, int logN, int log_batch,
 // ones are faster with non-temporal stores (2^10 x 2^12: 8.2 and 8.7; 2^14 x 2^14: 185
 // and 189).  At 16 terms the operands need that cache as well: FP32 outputs from
 // 128 MiB (2^11 x 2^13 in a loop over circuits: 18.8 us, ordinary stores 19.5), rows
-// of at most 2^16 columns (2^7 x 2^18: 29 and 37 us), FP64 outputs of 256 MiB up to
+// of at most 2^16 columns (2^7 x 2^18: 29 and 37 us) and at most 2^17 rows (2^18 x
+// 2^6 FP64 outputs: 28.8 and 31.2), FP64 arithmetic with 256 MiB of outputs up to
 // 2^15 rows (2^15 x 2^10: 56 and 49; 2^16 x 2^9: 59 and 65).
 inline bool rows_plain_stores(int nS, int logM, int logN, bool f64, bool f64_out) {
   const int log_bytes = logM + logN + (f64_out ? 3 : 2);
   if (log_bytes < 26 || log_bytes > 28) return false;
-  return nS < 2 || (logN <= 16 && (f64_out || log_bytes > 26) && (!f64 || log_bytes < 28 || logM <= 15));
+  return nS < 2 || (logN <= 16 && logM <= (f64 && log_bytes == 28 ? 15 : 17) && (f64_out || log_bytes > 26));
 }
 // Waves of a step: one FP64 partial each in a final step, four per block.
 int64_t rows_units(const ContractArgs &a);
