@@ -391,7 +391,7 @@ static Status launch_rows_p(const char *nm, const ContractArgs &a, hipStream_t s
 
 template <typename O, int MODE, int C>
 static Status launch_rows_c(const char *nm, const ContractArgs &a, hipStream_t s) {
-  if (MODE == kModeIntermediate || rows_plain_stores(a.nS, a.logM, a.logN, false, sizeof(O) == 8))
+  if (MODE == kModeIntermediate || rows_plain_stores(a.nS, a.logM, a.logN, sizeof(O) == 8))
     return launch_rows_p<O, MODE, C, true>(nm, a, s);
   return launch_rows_p<O, MODE, C, MODE == kModeIntermediate>(nm, a, s);
 }
@@ -428,7 +428,7 @@ Status launch_rows_f64(const ContractArgs &a, hipStream_t s) {
   if (a.rows != 2 || a.nS > 2 || a.logM < 4 || a.logN < 7 || a.mode == kModeFinalDeposit)
     return Status::fail(CQC_ERR_INVALID_ARG, "row contraction: step shape");
   if (a.mode == kModeIntermediate) return launch_rows_f64_m<kModeIntermediate, true>(a, s);
-  return rows_plain_stores(a.nS, a.logM, a.logN, true, true) ? launch_rows_f64_m<kModeFinalBlocked, true>(a, s)
+  return rows_plain_stores(a.nS, a.logM, a.logN, true) ? launch_rows_f64_m<kModeFinalBlocked, true>(a, s)
                                                              : launch_rows_f64_m<kModeFinalBlocked, false>(a, s);
 }
 

@@ -277,20 +277,19 @@ __host__ __device__ inline int rows_log_tiles(int logM, int logN, int log_batch,
   if (lt > 14 - logN) lt = 14 - logN;
   return lt < 0 ? 0 : lt;
 }
-// Whether a single call's final row kernel writes with ordinary stores.
-// Outputs of 64 to 256 MiB stay in the 256 MiB last-level cache, so that the
-// write-back overlaps what follows: 2^12 x 2^14 FP32 outputs of one term 44 us,
-// 50 with non-temporal stores; 2^9 x 2^16 FP64 ones 46 and 54.  Smaller and larger
-// ones are faster with non-temporal stores (2^10 x 2^12: 8.2 and 8.7; 2^14 x 2^14: 185
-// and 189).  At 16 terms the operands need that cache as well: FP32 outputs from
-// 128 MiB (2^11 x 2^13 in a loop over circuits: 18.8 us, ordinary stores 19.5), rows
-// of at most 2^16 columns (2^7 x 2^18: 29 and 37 us) and at most 2^17 rows (2^18 x
-// 2^6 FP64 outputs: 28.8 and 31.2), FP64 arithmetic with 256 MiB of outputs up to
-// 2^15 rows (2^15 x 2^10: 56 and 49; 2^16 x 2^9: 59 and 65).
-inline bool rows_plain_stores(int nS, int logM, int logN, bool f64, bool f64_out) {
+// Whether a single call's final row kernel writes with ordinary stores: outputs
+// of 64 to 256 MiB with fewer than 16 terms.  They stay in the 256 MiB last-level
+// cache, so that a loop that writes one buffer again and again is faster - 2^12 x
+// 2^14 FP32 outputs of one term 44 us, 50 with non-temporal stores; 2^9 x 2^16 FP64
+// ones 46 and 54 - and calls on buffers in turn are little slower: 51 and 50, 55 and
+// 54.  Smaller and larger outputs are faster with non-temporal stores (2^10 x 2^12:
+// 8.2 and 8.7; 2^14 x 2^14: 185 and 189), rows of 2^18 columns too (2^6 x 2^18, four
+// terms: 15.7 and 17.3 on buffers in turn), and with 16 terms the operands need
+// that cache (2^13 x 2^11 FP64 outputs: ordinary stores 27.5 us and non-temporal ones
+// 30 in one buffer, 34.6 and 29.6 on buffers in turn).
+inline bool rows_plain_stores(int nS, int logM, int logN, bool f64_out) {
   const int log_bytes = logM + logN + (f64_out ? 3 : 2);
-  if (log_bytes < 26 || log_bytes > 28) return false;
-  return nS < 2 || (logN <= 16 && logM <= (f64 && log_bytes == 28 ? 15 : 17) && (f64_out || log_bytes > 26));
+  return nS < 2 && logN <= 17 && log_bytes >= 26 && log_bytes <= 28;
 }
 // Waves of a step: one FP64 partial each in a final step, four per block.
 int64_t rows_units(const ContractArgs &a);
