@@ -47,8 +47,8 @@ WORKLOAD = {
 
 # kernel sources whose change invalidates a committed HBM-counter record
 TRAFFIC_SOURCES = {
-    "c2": ["paper_2012_02333_amd/csrc/k_contract.hip", "paper_2012_02333_amd/csrc/kernels.hpp"],
-    "c3": ["paper_2012_02333_amd/csrc/k_wide.hip", "paper_2012_02333_amd/csrc/kernels.hpp"],
+    "c2": ["paper_2012_02333_amd/csrc/k_rows.hip", "paper_2012_02333_amd/csrc/kernels.hpp"],
+    "c3": ["paper_2012_02333_amd/csrc/k_panel.hip", "paper_2012_02333_amd/csrc/kernels.hpp"],
 }
 
 
