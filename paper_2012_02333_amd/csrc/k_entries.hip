@@ -63,14 +63,16 @@ __device__ __forceinline__ void mode_products(double (&u)[1 << (2 * KIN)]) {
 // Subcircuits with one or two incoming cuts and no outgoing one, FP32 in and
 // out: four adjacent columns per thread.  Bound by its bytes, half read, half
 // written; with one column per thread (4 bytes per access) 2^22 columns of two
-// cuts took 146 us, with four 83 (125 when four sets of buffers take turns).  The
-// columns take turns in the FP64 products, so only the 4 x 4^KIN floats stay in
-// registers.  Ordinary loads: the variants may be in the caches, where they were
-// just written (2^21 columns: 45 us, non-temporal loads 58, one column per thread
-// 44).  FP64 keeps the general kernel, whose accesses are 8 bytes wide.
+// cuts took 146 us, with four 118.  The columns take turns in the FP64 products,
+// so only the 4 x 4^KIN floats stay in registers.  NT: non-temporal loads, for
+// variants that do not fit beside the entries in the 256 MiB last-level cache;
+// smaller ones may be there, where they were just written (2^21 columns of two
+// cuts: 45 us, non-temporal 58, one column per thread 44; four sets of buffers in
+// turn: 63, 61 and 72).  FP64 keeps the general kernel, whose accesses are 8 bytes
+// wide.
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
-template <int KIN, int EIGEN>
+template <int KIN, int EIGEN, bool NT>
 __global__ __launch_bounds__(256) void k_build_entries_in(const EntryArgs a) {
   constexpr int NI = 1 << (2 * KIN);
   const int64_t x = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x), nx = int64_t(1) << a.f;
@@ -79,7 +81,11 @@ __global__ __launch_bounds__(256) void k_build_entries_in(const EntryArgs a) {
   float *E = static_cast<float *>(a.E) + x;
   f32x4u v[NI];
 #pragma unroll
-  for (int i = 0; i < NI; ++i) v[i] = *reinterpret_cast<const f32x4u *>(V + i * nx);
+  for (int i = 0; i < NI; ++i) {
+    const f32x4u *p = reinterpret_cast<const f32x4u *>(V + i * nx);
+    if constexpr (NT) v[i] = __builtin_nontemporal_load(p);
+    else v[i] = *p;
+  }
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     double u[NI];
@@ -254,9 +260,14 @@ template <int EIGEN>
 static Status launch_entries_f32(const EntryArgs &a, hipStream_t s) {
   const int64_t nx = int64_t(1) << a.f;
   const dim3 b(256), gi((unsigned)((nx / 4 + 255) / 256)), go((unsigned)((nx / 2 + 255) / 256));
-  if (a.k_out == 0)
-    return a.k_in == 1 ? launch("build_entries", k_build_entries_in<1, EIGEN>, gi, b, 0, s, a)
-                       : launch("build_entries", k_build_entries_in<2, EIGEN>, gi, b, 0, s, a);
+  if (a.k_out == 0) {
+    const bool nt = (nx << (2 * a.k_in + 2)) > (int64_t(128) << 20);   // bytes of the variants
+    if (a.k_in == 1)
+      return nt ? launch("build_entries", k_build_entries_in<1, EIGEN, true>, gi, b, 0, s, a)
+                : launch("build_entries", k_build_entries_in<1, EIGEN, false>, gi, b, 0, s, a);
+    return nt ? launch("build_entries", k_build_entries_in<2, EIGEN, true>, gi, b, 0, s, a)
+              : launch("build_entries", k_build_entries_in<2, EIGEN, false>, gi, b, 0, s, a);
+  }
   return a.k_out == 1 ? launch("build_entries", k_build_entries_out<1, EIGEN>, go, b, 0, s, a)
                       : launch("build_entries", k_build_entries_out<2, EIGEN>, go, b, 0, s, a);
 }

@@ -181,3 +181,17 @@ def test_one_sided_cuts_fp32(kinds, f, form):
     got = E.double().cpu().numpy()
     assert np.all(np.abs(got - ref) <= 2.0 ** -24 * np.abs(ref) + 1e-13)
     assert float(eb[0]) == 7.0 and float(eb[-1]) == 7.0
+
+
+@pytest.mark.parametrize("kinds,f", [([0, 0], 21), ([0, 0], 22), ([0], 23), ([0], 24)])
+@pytest.mark.parametrize("form", ["pauli", "eigen"])
+def test_incoming_cuts_fp32_either_side_of_the_load_rule(kinds, f, form):
+    """Variants of up to 128 MiB and beyond: the FP64 output of the general
+    kernel, rounded once."""
+    _gpu()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(60 + f)
+    V = torch.rand((4 ** len(kinds), 1, 2 ** f, 1), device="cuda", generator=g)
+    (E,) = cqc.build_entries([(V, kinds)], form=form)
+    (E64,) = cqc.build_entries([(V, kinds)], out_dtype=torch.float64, form=form)
+    assert torch.equal(E, E64.float())
