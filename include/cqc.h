@@ -171,9 +171,9 @@ int cqc_batch_destroy(cqc_batch batch);
  * NULL: p is then not written at all.  losses: HOST array of n_inst DEVICE
  * pointers, or NULL; losses[i] (if set) receives
  *     L_i = -sum_x t_x log max(p_x, 1e-30)
- * (logarithms in the output precision - FP32 outputs: about 1e-7 relative
- * per term, the size of p's own rounding - and the terms summed in FP64 in
- * the fixed order of the mass, so L_i is bitwise reproducible).  An instance with
+ * (logarithms in the output precision - FP32 outputs: within 2^-23 relative
+ * of each logarithm - and the terms summed in FP64 in the fixed order of the
+ * mass, so L_i is bitwise reproducible).  An instance with
  * a loss must have inst[i].mass NULL; without one, inst[i].mass works as in
  * cqc_batch_create.  grads[i] may equal targets[i] (each element is read
  * before it is overwritten); no other two of the buffers may overlap.  The

@@ -26,10 +26,10 @@
 // SIMD do not finish together, and a launch of exactly one unit per slot lost
 // 15% to its ends.
 // The final step of a 30-qubit, six-cut chain (2^18 x 2^12 outputs, 64 terms)
-// within a call: 1770 us on the LDS-staged wide kernel, 1530 us here.  By
-// itself on random operands 1380 us, 1080 us without its stores, 990 us for
-// the products alone; with the 4 GiB of stores the clock falls from 2.4 to
-// 2.0 GHz, so power holds most of the rest.
+// within a call of n = 30: 1740 us on the LDS-staged wide kernel, 1310 to 1460
+// here, the call 1743 and 1390 us.  Counters: matrix cores 0.77 busy at a shader
+// clock of 1.86 GHz, where the products alone would take 1130 us.  By itself on
+// random operands 1380 us, 1080 us without its stores.
 #include <algorithm>
 
 #include "kdev.hpp"
