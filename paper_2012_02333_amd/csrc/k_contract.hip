@@ -361,13 +361,14 @@ __device__ __forceinline__ void contract_small_tile(const ContractArgs &a, uint3
   // Masked loads, or (`every`) unconditional ones as in contract_tile (column 0
   // where the tile overhangs, row 0 for a missing term) whose missing terms are
   // zeroed afterwards.  Unconditional: on the smaller tiles in FP32 or with all
-  // 16 terms (2^18 x 2^6 FP64 outputs 53 us, masked 56), for FP64 outputs of the
-  // 64 x 256 tile in deposit order (2^13 x 2^11: 144, masked 155) and in the
-  // cross-entropy form.  Elsewhere they cost registers, load rows in place of
-  // missing terms and crowd scattered stores: 2^18 x 2^6 FP64 outputs of one
-  // term 39.5 us, masked 36.2; on the 64 x 256 tile 2^11 x 2^13 FP32 outputs of
-  // FP64 entries 23.3 and 20.3, 2^13 x 2^11 in deposit order 84.5 and 69.5.
-  const bool every = XE != 0 || (BMB * BNB <= 4 ? sizeof(T) == 4 || nSv == 16 : MODE == kModeFinalDeposit && sizeof(O) == 8);
+  // 16 terms (2^18 x 2^6 FP64 outputs 53 us, masked 56) and in the cross-entropy
+  // form.  Elsewhere they cost registers, load rows in place of missing terms
+  // and crowd scattered stores: 2^18 x 2^6 FP64 outputs of one term 39.5 us,
+  // masked 36.2; on the 64 x 256 tile 2^11 x 2^13 FP32 outputs of FP64 entries
+  // 23.3 and 20.3, in deposit order 2^13 x 2^11 FP32 outputs 84.5 and 69.5; 2^22
+  // to 2^24 FP64 outputs in reversed order 1.09 times the masked loads' time on
+  // average over their shapes (0.93 to 1.54), in random orders 1.00 to 1.03.
+  const bool every = XE != 0 || (BMB * BNB <= 4 && (sizeof(T) == 4 || nSv == 16));
   auto load_ops = [&]() {
     if (every) {
 #pragma unroll
@@ -812,7 +813,12 @@ int choose_tile(Acc acc, int nS, int logM, int logN, bool wide_ok, bool panel, i
     return kTileW;
   // at least one block per CU where the step has that many outputs: 2^19 in
   // deposit order (16 terms) took 13.5 us on 32 blocks of 64 x 256, 7.7 on
-  // 512 of 16 x 64
+  // 512 of 16 x 64.  Over shapes, FP32 and FP64 and orders, deposits of 4 to 64
+  // terms take 0.48 to 0.97 of the large tiles' time up to 2^20 outputs; at 2^21
+  // (512 blocks of 32 x 128 for 128) 0.87 on average of 4 terms and 0.79 of 64,
+  // though single orders are slower (reversed, 2^9 x 2^12 FP32: 23 and 44 us):
+  // which scattered stores meet in time decides there, and no property of the
+  // order that tells was found
   auto fills = [&](int64_t bm, int64_t bn) { return !spread || (M / bm) * (N / bn) * nbatch >= 256; };
   if (M >= 64 && N >= 256 && fills(64, 256)) return kTileL;
   if (N < 64 && M >= 256) return kTileT;
